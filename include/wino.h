@@ -69,9 +69,10 @@ typedef struct wino_plan_s wino_plan_t; /* opaque, immutable after creation */
  * work-groups (no partials scratch in the workspace; see
  * wino_workspace_bytes). */
 #define WINO_NO_SPLIT 2u
-/* Keep the forward of an F(4^3, 3^3) layer with at most 64 kernels in two
- * stages (input transform to the workspace, then the product) instead of
- * fusing the input transform into the product (see wino_forward). */
+/* Keep the forward of an F(4^3, 3^3) layer with at most 64 kernels, or of an
+ * F(2^3, 3^3) layer that wino_forward would run in one kernel, in two stages
+ * (input transform to the workspace, then the product) instead of fusing the
+ * input transform into the product (see wino_forward). */
 #define WINO_NO_FUSE 8u
 
 typedef struct {
@@ -272,7 +273,12 @@ wino_status wino_gemm_inverse(const wino_plan_t* plan, void* workspace, size_t w
 
 /* The whole forward (eq. 4 with eq. 5) on one stream, with
  * wino_forward_workspace_bytes(plan) bytes of workspace (workspace may be
- * NULL when that is 0).  Two-stage plans run wino_transform_input and then
+ * NULL when that is 0).  F(2^3, 3^3) plans with the default points, whole
+ * groups of 16 channels, pad 1 and a multiple of 4 along the last axis (x at
+ * most 512 MiB) form the transformed input inside the product as well; their
+ * workspace holds the kernels split for it instead of V, so the
+ * wino_transform_input + wino_gemm_inverse pair may differ from wino_forward
+ * in the last bits.  Other two-stage plans run wino_transform_input and then
  * wino_gemm_inverse; fused plans (F(4^3, 3^3), at most 64 kernels) form
  * each tile block's transformed input in LDS inside the product, 8 channels
  * at a time, so V never reaches memory (§4.1's reshuffle and §4.3's

@@ -10,6 +10,7 @@
 
 #include "gemm_acc.hpp"
 #include "gemm_acc4.hpp"
+#include "gemm_split.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
 #include "synth.hpp"
@@ -46,6 +47,10 @@ struct SizeOps {
   // 2: (2, 2, 2); y pooled), null for sizes without one; part as for gemm
   wino_status (*gemm_pool)(const wino_plan_s&, const float* V, float* part, const float* U, const float* bias,
                            float* y, int pool, hipStream_t);
+  // the whole forward of a plan with fwd_split (null for sizes without one);
+  // ws: the plan's workspace, pool: 0 or 2 (window (2, 2, 2), y pooled)
+  wino_status (*fwd_split)(const wino_plan_s&, const float* x, const float* U, const float* bias, float* y,
+                           float* ws, int pool, hipStream_t);
 };
 
 template <int N, int MM, int R, bool CONST>
@@ -198,6 +203,58 @@ struct Launch {
     }
   }
 
+  // F(2^3, 3^3): the kernels split into the workspace (V's place), then the
+  // forward in one kernel and the tail blocks' sum.
+  static wino_status fwd_split(const wino_plan_s& p, const float* x, const float* U, const float* bias, float* y,
+                               float* ws, int pool, hipStream_t s) {
+    if constexpr (N == 3 && MM == 2 && CONST) {
+      using G = SplitGeom<N, MM, R>;
+      u32x4* const P = reinterpret_cast<u32x4*>(ws);
+      const int64_t n8 = int64_t(NXI) * (p.C_pad / 8) * p.K_pad;
+      hipLaunchKernelGGL(k_split_u, dim3(p.grid_split_u), dim3(256), 0, s, U, P, n8, int32_t(p.K_pad));
+      FuseArgs a{};
+      acc_args(p, a.g, G::TB, bias, ws + p.v_floats);
+      a.g.nparts = split_parts<G>(p);
+      a.C = p.C;
+      int64_t xs = 1;
+      for (int i = 0; i < 3; ++i) {
+        a.X[i] = int32_t(p.X[i]); a.pad[i] = p.pad[i];
+        xs *= p.X[i];
+      }
+      a.xstride = uint32_t(xs * 4);
+      a.xbytes = uint32_t(xs * 4 * p.C * p.batch);
+      if (pool == 0) {
+        hipLaunchKernelGGL((k_fwd_split<0>), dim3(p.grid_gemm), dim3(G::NT), 0, s, x, P, y, a);
+        if (a.g.nparts > 1)
+          hipLaunchKernelGGL((k_part_reduce<N, MM, G::TB, G::KB>), dim3(p.grid_reduce), dim3(256), 0, s, y, a.g,
+                             int32_t(p.ntail));
+      } else {
+        pool_args(p, a.g);
+        hipLaunchKernelGGL((k_fwd_split<1>), dim3(p.grid_gemm), dim3(G::NT), 0, s, x, P, y, a);
+        if (a.g.nparts > 1)
+          hipLaunchKernelGGL((k_part_reduce_pool<N, MM, G::TB, G::KB>), dim3(p.grid_reduce / G::NOUT), dim3(256), 0,
+                             s, y, a.g, int32_t(p.ntail));
+      }
+      return launch_status();
+    } else {
+      return WINO_EUNSUPPORTED;
+    }
+  }
+
+  // Parts of a tail block of the split product: the planner's, at most one
+  // per (pass, channel stage) step.
+  template <class G>
+  static int split_parts(const wino_plan_s& p) {
+    const int64_t steps = int64_t(G::NPASS) * (p.C_pad / G::SC);
+    return int(p.nparts < steps ? p.nparts : steps);
+  }
+
+  // Pooled extents of window (2, 2, 2), floor rounding.
+  static void pool_args(const wino_plan_s& p, AccArgs& a) {
+    for (int i = 0; i < 3; ++i) a.Yp[i] = int32_t(p.Y[i] / 2);
+    a.ystride_p = int64_t(a.Yp[0]) * a.Yp[1] * a.Yp[2];
+  }
+
   // Arguments of k_gemm_inv; pool > 0 adds the pooled extents (floor rounding).
   static GemmArgs gemm_args(const wino_plan_s& p, const float* bias, int pool) {
     GemmArgs g{};
@@ -231,8 +288,7 @@ struct Launch {
       using G = AccGeom<N, MM, R>;
       AccArgs a{};
       acc_args(p, a, G::TB, bias, part);
-      for (int i = 0; i < 3; ++i) a.Yp[i] = int32_t(p.Y[i] / 2);
-      a.ystride_p = int64_t(a.Yp[0]) * a.Yp[1] * a.Yp[2];
+      pool_args(p, a);
       hipLaunchKernelGGL((k_gemm_acc<N, MM, R, CONST, 1>), dim3(p.grid_gemm), dim3(G::NT), 0, s, V, U, y, a,
                          p.fm);
       if (p.nparts > 1)
@@ -262,7 +318,7 @@ constexpr SizeOps make_ops() {
   if constexpr (N == 3 && MM == 4 && R == 3)
     return SizeOps{&L::filter, &L::input, &L::gemm, &L::wgrad, &L::fused, &L::gemm_pool};
   else if constexpr (N == 3 && MM == 2)
-    return SizeOps{&L::filter, &L::input, &L::gemm, &L::wgrad, nullptr, &L::gemm_pool};
+    return SizeOps{&L::filter, &L::input, &L::gemm, &L::wgrad, nullptr, &L::gemm_pool, &L::fwd_split};
   else
     return SizeOps{&L::filter, &L::input, &L::gemm, &L::wgrad, nullptr};
 }

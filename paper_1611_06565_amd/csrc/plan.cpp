@@ -150,6 +150,27 @@ bool acc_geometry(wino_plan_s& p, const SizeTraits& t, bool split, int cus) {
   return true;
 }
 
+// Whether an F(2^3, 3^3) forward runs as one kernel that forms V in LDS
+// (k_fwd_split), and the grid that splits its kernels.  The kernel's input
+// windows are whole 16-byte units of the last axis (pad 1, a multiple of 4),
+// its steps whole groups of 16 channels, its matrices the default ones, its
+// offsets into x 32-bit with room above the buffer for the masked rows, and
+// the split kernels (three bf16 for each of U's floats) take V's place in the
+// workspace.  Everything else runs in two stages.  Measured both ways (us, one
+// stage against two): 8 x 64 x 16 x 56 x 56 to 128 kernels 535 / 685, its data
+// gradient (128 to 64) 530 / 858.
+void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
+  p.fwd_split = false;
+  if (p.N != 3 || p.kind != 0 || !p.const_mats || (p.flags & WINO_NO_FUSE)) return;
+  if (p.pad[2] != 1 || p.X[2] % 4 != 0 || p.C % 16 != 0) return;
+  const int64_t lim = int64_t(1) << 27;             // floats of x: 2^29 bytes
+  int64_t xs = 0, xn = 0;
+  if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xs) || !mul3_ok(xs, int64_t(p.C), p.batch, &xn) || xn > lim) return;
+  if (uf / 2 * 3 > p.v_floats) return;
+  if (!grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
+  p.fwd_split = true;
+}
+
 // Weight-gradient geometry (F(r, m) on the forward's points, V reused): the
 // transformed output gradients D, the partial products of the tile ranges
 // and the grids of its four kernels.  Leaves wgrad_ok false when F(r, m)'s
@@ -417,6 +438,7 @@ wino_status wino_plan(int N, int m, int r, int C, int K, const int64_t* dims, co
     }
   p.fm = to_fmats(R);
   p.const_mats = defaults;
+  fwd_split_geometry(p, uf);
   wgrad_geometry(p, t, pts, R);
 
   wino_plan_s* h = new (std::nothrow) wino_plan_s(p);

@@ -58,6 +58,10 @@ struct wino_plan_s {
   // (k_fused43, one work-group per 16 tiles x 16 kernels) and needs no workspace
   bool fused;
   uint32_t grid_fused;
+  // F(2^3, 3^3): the forward forms V inside the product (k_fwd_split); the
+  // split kernels take the place of V in the workspace
+  bool fwd_split;
+  uint32_t grid_split_u;  // k_split_u (256 threads)
 };
 
 namespace wino {

@@ -148,6 +148,13 @@ wino_status wino_forward_ex(const wino_plan_t* p, const float* x, const float* U
   if (ws == nullptr) return WINO_EINVAL;
   if (!aligned16(ws)) return WINO_EINVAL;
   if (ws_bytes < wino_workspace_bytes(p)) return WINO_EWORKSPACE;
+  if (p->fwd_split) {
+    // F(2^3): the input transform runs inside the product here too, with the
+    // split kernels in the workspace
+    const SizeOps* ops = ops_of(*p);
+    if (ops == nullptr || ops->fwd_split == nullptr) return WINO_EUNSUPPORTED;
+    return ops->fwd_split(*p, x, U, bias, y, static_cast<float*>(ws), 0, static_cast<hipStream_t>(stream));
+  }
   wino_status st = wino_transform_input(p, x, ws, ws_bytes, stream);
   if (st != WINO_OK) return st;
   return wino_gemm_inverse_ex(p, ws, ws_bytes, U, bias, y, stream);
@@ -197,6 +204,7 @@ wino_status wino_forward_pool(const wino_plan_t* p, const float* x, const float*
   if (ws == nullptr) return WINO_EINVAL;
   if (!aligned16(ws)) return WINO_EINVAL;
   if (ws_bytes < wino_workspace_bytes(p)) return WINO_EWORKSPACE;
+  if (p->fwd_split) return ops->fwd_split(*p, x, U, bias, y, static_cast<float*>(ws), pool, s);
   float* V = static_cast<float*>(ws);
   float* part = p->nparts > 1 ? V + p->v_floats : nullptr;
   const wino_status st = ops->input(*p, x, V, s);

@@ -1,0 +1,77 @@
+"""F(2^3, 3^3) forward in one kernel (bf16-split products, V formed in LDS):
+every output against the fp64 direct correlation at the sizes where its blocks,
+steps and row loads change, and the layers just outside its rule beside them.
+
+The bar is the library's for m = 2 (1e-5 of the summed magnitudes): the split
+leaves out terms below 2^-22 of a product and otherwise rounds in fp32."""
+import numpy as np
+import pytest
+
+from gpu_util import check_full, run_layer
+from workloads import LayerSpec, draw_layer
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(name, batch, C, K, X, pad=1, **kw):
+    return LayerSpec(name, N=3, m=2, r=3, batch=batch, C=C, K=K, X=X, pad=pad, x_dist="normal", w_dist="he", **kw)
+
+
+INSIDE = [
+    layer("one_pair_of_tiles", 1, 16, 1, (1, 1, 4)),              # smallest: two tiles, one kernel, one stage
+    layer("odd_first_axes", 2, 32, 70, (3, 5, 8), relu=True),     # cropped tiles, ragged kernel block
+    layer("ragged_tile_block", 3, 48, 64, (5, 7, 12), leaky=0.2),  # T past a whole block, three stages
+    layer("rows_of_33_tiles", 1, 16, 130, (4, 6, 132)),           # rows longer than a wave's 32 tiles
+    layer("rows_of_32_tiles", 2, 64, 128, (4, 4, 64)),            # rows end where the wave's tiles do
+    layer("whole_blocks", 8, 32, 64, (16, 56, 56)),               # full rounds and a split tail
+]
+OUTSIDE = [
+    layer("row_not_of_4", 2, 32, 70, (3, 5, 10)),
+    layer("channels_not_of_16", 2, 24, 64, (4, 6, 8)),
+    layer("no_padding", 2, 32, 64, (6, 7, 8), pad=0),
+    layer("kernels_split_larger_than_v", 1, 16, 400, (2, 4, 8)),
+]
+
+
+@pytest.mark.parametrize("split", [True, False], ids=["parts", "whole"])
+@pytest.mark.parametrize("spec", INSIDE + OUTSIDE, ids=lambda s: s.name)
+def test_full_output(spec, split):
+    x, w = draw_layer(spec, seed=41)
+    b = (np.random.default_rng(2).standard_normal(spec.K) * 0.3).astype(np.float32)
+    y, _ = run_layer(spec, x, w, bias=b, guard=1024, split=split)
+    check_full(spec, y, x, w, bias=b)
+
+
+def test_pads_of_the_leading_axes():
+    """The rule asks for pad 1 on the last axis only."""
+    import torch
+
+    from oracle.direct import direct_blas
+    from oracle.metric import normalised_error
+    from paper_1611_06565_amd.wino import Plan
+    spec = layer("pads_0_2_1", 2, 32, 64, (6, 5, 8))
+    x, w = draw_layer(spec, seed=5)
+    plan = Plan(3, 2, 3, 32, 64, [2, 6, 5, 8], pad=[0, 2, 1])
+    y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda())).cpu().numpy()
+    xp = np.pad(x, ((0, 0), (0, 0), (0, 0), (2, 2), (1, 1)))
+    ref, den = direct_blas(xp, w, 0)
+    assert normalised_error(y, ref, den)["max"] <= 1e-5
+
+
+def test_error_no_larger_than_two_stages():
+    """Against fp64 the split products are at least as close as the fp32 ones."""
+    import torch
+
+    from oracle.direct import direct_blas
+    from paper_1611_06565_amd.wino import Plan
+    for C, dist in ((16, "normal"), (64, "relu_normal"), (256, "uniform")):
+        spec = layer("err", 1, C, 64, (6, 8, 16)).with_(x_dist=dist)
+        x, w = draw_layer(spec, seed=9)
+        ref, _ = direct_blas(x, w, 1)
+        err = []
+        for fuse in (True, False):
+            plan = Plan(3, 2, 3, C, 64, [1, 6, 8, 16], pad=1, fuse=fuse)
+            y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda()))
+            err.append(np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref))
+        print(C, dist, err)
+        assert err[0] <= 1.05 * err[1], (C, dist, err)
