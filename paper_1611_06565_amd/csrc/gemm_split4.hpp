@@ -1,0 +1,219 @@
+// Batched GEMM with the inverse transform of F(4^2, 3^2) on the bf16 matrix
+// cores (fp32 operands split into three bf16 each, gemm_split.hpp), all 36
+// elements resident.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "gemm_acc.hpp"
+#include "gemm_split.hpp"
+#include "kernels.hpp"
+#include "synth.hpp"
+#include "transforms.hpp"
+
+namespace wino {
+
+template <int N, int MM, int R>
+struct Split4Geom {
+  static constexpr int A = MM + R - 1;
+  static constexpr int NXI = ipow(A, N);
+  static constexpr int NOUT = ipow(MM, N);
+  static constexpr int TB = 64, KB = 32;          // tiles and kernels per work-group
+  static constexpr int NW = 12, NT = 768;
+  static constexpr int E = NXI / NW;              // elements per wave
+  static constexpr int SC = 16;                   // channels per step
+  static constexpr int HT = 32;                   // tiles per epilogue round
+  static constexpr int LDK = HT * MM + 4;         // stitch: floats per (o0, kernel), padded
+  static_assert(N == 2 && MM == 4 && A == 6 && E * NW == NXI, "F(4^2, 3^2)");
+  static_assert(MM * KB * LDK <= NXI * HT * KB, "the stitch fits the exchange");
+};
+
+// One work-group: 64 tiles x 32 kernels, twelve waves; wave w owns elements
+// 3w .. 3w + 2 (96 accumulators), so every V and U value of the block is
+// loaded and split by exactly one wave, straight from global memory to
+// registers: lane (row r, half h) takes channels 8h .. 8h + 7 of a 16-channel
+// step for both operands.  No barrier until the channels are done.  Then the
+// products of 32 tiles at a time meet in LDS (144 KB), a thread applies A^T to
+// two (tile, kernel) pairs, and the outputs go through LDS once more so that
+// neighbouring lanes store neighbouring tiles' rows, 16 bytes each.
+//
+// What bounds it: the sum of its parts, which hardly overlap (on 64 x 256 x
+// 56 x 56, K = 256, 535-575 us: matrix work 200 at the clock it falls to, the
+// splits' vector work about 135, the loads' addresses about 160, the
+// epilogues about 60).  A 64 x 64 block would take a third off the loads and
+// splits, but its 36 elements do not fit the registers.  Against the fp32
+// passes of k_gemm_acc4 (us, there / here): that layer 581 / 536;
+// 64 x 512 x 28 x 28, K = 128, 205 / 133; 16 x 16 x 112 x 112, K = 64, 43 / 31;
+// 1 x 3 x 224 x 224, K = 64, 39 / 16.  V is loaded temporally: the kernel
+// blocks of a tile block re-read it (570 -> 531 us against non-temporal loads;
+// the next input transform then finds less of x in the memory-side cache and
+// gives the 40 us back where x is the same tensor each time).
+template <int N, int MM, int R>
+__global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict__ V, const float* __restrict__ U,
+                                                        float* __restrict__ y, AccArgs g) {
+  using G = Split4Geom<N, MM, R>;
+  constexpr int NXI = G::NXI, NOUT = G::NOUT, TB = G::TB, KB = G::KB, E = G::E, HT = G::HT;
+  __shared__ __attribute__((aligned(16))) float ex[NXI * HT * KB];
+
+  const int tid = int(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, half = lane >> 5;
+
+  // Work unit -> (block, channel stages): blocks and tail blocks as in
+  // k_gemm_acc, a tail block's parts are runs of its channel stages (the
+  // inverse transform is linear in them).
+  const int xcd = int(blockIdx.x) & 7, j = int(blockIdx.x) >> 3;
+  const int xn = g.xn[xcd], xs = g.xs[xcd], np = g.nparts;
+  const int nwhole = xn - xs;
+  if (j >= nwhole + xs * np) return;
+  const bool tail = np > 1 && j >= nwhole;
+  const int tj = j >= nwhole ? j - nwhole : 0;
+  const int blk = g.xb0[xcd] + (j >= nwhole ? nwhole + tj / np : j);
+  const int nstage = g.C_pad / G::SC;
+  const int q = tail ? tj % np : 0;
+  const int s0 = tail ? nstage * q / np : 0;
+  const int s1 = tail ? nstage * (q + 1) / np : nstage;
+  const int64_t pslot = tail ? int64_t(g.xt0[xcd]) * np + tj : 0;
+  const int tb = blk / g.nkb, kb = blk % g.nkb;
+
+  constexpr int64_t VX = TB * 4, VG = int64_t(NXI) * TB * 4;      // V element / group strides (floats)
+  const int64_t UG = int64_t(g.K_pad) * 4;                        // U group stride
+  const uint32_t vlane = uint32_t(half) * uint32_t(2 * VG * 4) + uint32_t(col) * 16u;
+  const uint32_t ulane = uint32_t(half) * uint32_t(2 * UG * 4) + uint32_t(col) * 16u;
+  const float* const vblk = V + int64_t(tb) * g.vblock + wave * E * VX;
+  const float* const ublk = U + int64_t(kb) * (KB * 4) + wave * E * g.uplane;
+
+  f32x4 ra[4], rb[2];                             // [32-tile half][group of the lane's half]
+  auto load = [&](int st, int e) {
+    const char* us = reinterpret_cast<const char*>(ublk + e * g.uplane + int64_t(st) * 4 * UG);
+    const char* vs = reinterpret_cast<const char*>(vblk + e * VX + int64_t(st) * 4 * VG);
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) rb[jj] = *reinterpret_cast<const f32x4*>(us + jj * UG * 4 + ulane);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj)
+        ra[2 * i + jj] = *reinterpret_cast<const f32x4*>(vs + jj * VG * 4 + vlane + i * 512);
+  };
+
+  f32x16 acc[E][2];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[e][i] = f32x16{};
+
+  if (s0 < s1) load(s0, 0);
+#pragma unroll 1
+  for (int st = s0; st < s1; ++st) {
+    // the loads past the last step read the last stage again
+    const int nx = st + 1 < s1 ? st + 1 : st;
+    static_for<E>([&](auto I) {
+      constexpr int e = decltype(I)::value;
+      const Split8 b = split8(rb[0], rb[1]);
+      const Split8 a0 = split8(ra[0], ra[1]), a1 = split8(ra[2], ra[3]);
+      load(e + 1 < E ? st : nx, (e + 1) % E);
+      // the small terms first
+      f32x16 c0 = acc[e][0], c1 = acc[e][1];
+      c0 = mfma_bf16(a0.l, b.h, c0);
+      c1 = mfma_bf16(a1.l, b.h, c1);
+      c0 = mfma_bf16(a0.h, b.l, c0);
+      c1 = mfma_bf16(a1.h, b.l, c1);
+      c0 = mfma_bf16(a0.m, b.m, c0);
+      c1 = mfma_bf16(a1.m, b.m, c1);
+      c0 = mfma_bf16(a0.m, b.h, c0);
+      c1 = mfma_bf16(a1.m, b.h, c1);
+      c0 = mfma_bf16(a0.h, b.m, c0);
+      c1 = mfma_bf16(a1.h, b.m, c1);
+      acc[e][0] = mfma_bf16(a0.h, b.h, c0);
+      acc[e][1] = mfma_bf16(a1.h, b.h, c1);
+    });
+  }
+
+  const MatRef<Which::AT, true, MM, R> AT{nullptr};
+  const bool quad = g.Y[1] % 4 == 0;              // rows of whole 16-byte units
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (i == 1) __syncthreads();                  // the first half's stores have read ex
+    // exchange: ex[element][slot q][lane][4], slot q of a wave's block = rows
+    // 8q + 4 half + 0..3 (tiles) of kernel col
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) {
+        const f32x16& c = acc[e][i];
+        *reinterpret_cast<f32x4*>(ex + (wave * E + e) * (HT * KB) + qq * 256 + lane * 4) =
+            f32x4{c[4 * qq], c[4 * qq + 1], c[4 * qq + 2], c[4 * qq + 3]};
+      }
+    __syncthreads();
+    // thread (q, lane, two rows): pairs (tiles t2, t2 + 1, kernel col)
+    const bool works = wave < 8;                  // 512 threads finish 1024 pairs
+    const int t2 = 8 * (wave >> 1) + 4 * half + 2 * (wave & 1);
+    float out[2][NOUT];
+    if (works) {
+      float m[2][NXI];
+#pragma unroll
+      for (int x = 0; x < NXI; ++x) {
+        const float2 v = *reinterpret_cast<const float2*>(ex + x * (HT * KB) + (wave >> 1) * 256 + lane * 4 + 2 * (wave & 1));
+        m[0][x] = v.x;
+        m[1][x] = v.y;
+      }
+#pragma unroll
+      for (int p = 0; p < 2; ++p) transform_nd<N, G::A, MM>(m[p], out[p], AT);
+    }
+    if (tail) {
+      // partial outputs of this unit: part[pslot][o][t][k], lanes over k
+      if (works) {
+        float* pp = g.part + pslot * NOUT * (TB * KB);
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) pp[(o * TB + i * HT + t2 + p) * KB + col] = out[p][o];
+      }
+      continue;
+    }
+    __syncthreads();                              // the products are read
+    if (works) {
+#pragma unroll
+      for (int o0 = 0; o0 < MM; ++o0)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          *reinterpret_cast<f32x4*>(ex + (o0 * KB + col) * G::LDK + (t2 + p) * MM) =
+              f32x4{out[p][o0 * MM], out[p][o0 * MM + 1], out[p][o0 * MM + 2], out[p][o0 * MM + 3]};
+    }
+    __syncthreads();
+    // thread = (tile, then kernel and output row): lanes over tiles
+    const int tl = tid % HT;
+    const int t = tb * TB + i * HT + tl;
+    if (t < g.T) {
+      int ti[3] = {0, 0, 0};
+      const int n = split_tile<N>(t, g.tiles, ti);
+      float* const yt = y + int64_t(n) * g.K * g.ystride_k + int64_t(ti[0] * MM) * g.Y[1] + ti[1] * MM;
+      const int left = g.Y[1] - ti[1] * MM;       // outputs of the row inside y
+#pragma unroll 1
+      for (int it = tid / HT; it < MM * KB; it += G::NT / HT) {
+        const int o0 = it / KB, kl = it % KB, kg = kb * KB + kl;
+        if (kg >= g.K || ti[0] * MM + o0 >= g.Y[0]) continue;
+        f32x4 v = *reinterpret_cast<const f32x4*>(ex + it * G::LDK + tl * MM);
+        const float bk = g.bias != nullptr ? g.bias[kg] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (g.bias != nullptr) v[k] += bk;
+          v[k] = activate(v[k], g.act, g.slope);
+        }
+        float* yo = yt + int64_t(kg) * g.ystride_k + int64_t(o0) * g.Y[1];
+        if (quad) {
+          __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(yo));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (k < left) __builtin_nontemporal_store(v[k], yo + k);
+        }
+      }
+    }
+  }
+}
+
+}  // namespace wino

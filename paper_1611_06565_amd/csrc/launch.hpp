@@ -11,6 +11,7 @@
 #include "gemm_acc.hpp"
 #include "gemm_acc4.hpp"
 #include "gemm_split.hpp"
+#include "gemm_split4.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
 #include "synth.hpp"
@@ -188,8 +189,14 @@ struct Launch {
       using G = Acc4Geom<N, MM, R>;
       AccArgs a{};
       acc_args(p, a, G::TB, bias, part);
-      hipLaunchKernelGGL((k_gemm_acc4<N, MM, R, CONST>), dim3(p.grid_gemm), dim3(G::NT), 0, s, V, U, y, a, p.fm);
-      if (p.nparts > 1)
+      if (CONST) {
+        a.nparts = split4_parts<Split4Geom<N, MM, R>>(p);
+        hipLaunchKernelGGL((k_gemm_split4<N, MM, R>), dim3(p.grid_gemm), dim3(Split4Geom<N, MM, R>::NT), 0, s, V, U,
+                           y, a);
+      } else {
+        hipLaunchKernelGGL((k_gemm_acc4<N, MM, R, CONST>), dim3(p.grid_gemm), dim3(G::NT), 0, s, V, U, y, a, p.fm);
+      }
+      if (a.nparts > 1)
         hipLaunchKernelGGL((k_part_reduce<N, MM, G::TB, G::KB>), dim3(p.grid_reduce), dim3(256), 0, s, y, a,
                            int32_t(p.ntail));
       return launch_status();
@@ -247,6 +254,18 @@ struct Launch {
   static int split_parts(const wino_plan_s& p) {
     const int64_t steps = int64_t(G::NPASS) * (p.C_pad / G::SC);
     return int(p.nparts < steps ? p.nparts : steps);
+  }
+
+  // Parts of a tail block of k_gemm_split4: the planner's, at most one per two
+  // channel stages, or per stage where fewer than 16 blocks leave the chip
+  // empty anyway (a part costs a whole partial output: 25 blocks of 2 stages
+  // 21 us in two parts, 18 whole; 2 blocks of 4 stages 15 us in four, 17 in two).
+  template <class G>
+  static int split4_parts(const wino_plan_s& p) {
+    const int nstage = p.C_pad / G::SC;
+    int most = p.ntail < 16 ? nstage : nstage / 2;
+    if (most < 1) most = 1;
+    return p.nparts < most ? p.nparts : most;
   }
 
   // Pooled extents of window (2, 2, 2), floor rounding.
