@@ -16,6 +16,7 @@
 #include "plan.hpp"
 #include "synth.hpp"
 #include "wgrad.hpp"
+#include "wgrad_split.hpp"
 #include "wino.h"
 
 namespace wino {
@@ -120,6 +121,9 @@ struct Launch {
     if constexpr ((BLK != 64 && BLK != 16) || CG != 4) {
       return WINO_EUNSUPPORTED;
     } else {
+      if constexpr (N == 3 && MM == 2 && CONST) {
+        if (p.wg_fused) return wgrad_split(p, x, dy, dw, ws, s);
+      }
       float* V = ws;
       float* D = ws + p.v_floats;
       float* part = D + p.wg_d_floats;
@@ -141,6 +145,37 @@ struct Launch {
                          p.fmw);
       return launch_status();
     }
+  }
+
+  // F(2^3, 3^3): both transforms inside the product (wgrad_split.hpp), the
+  // partial products at the start of the workspace.
+  static wino_status wgrad_split(const wino_plan_s& p, const float* x, const float* dy, float* dw, float* ws,
+                                 hipStream_t s) {
+    WgSplitArgs g{};
+    WgArgs a{};
+    a.K = g.K = p.K; a.C = g.C = p.C;
+    a.nkb = (p.wg_kpad4 + 63) / 64; a.ncb = (p.C_pad + 63) / 64;
+    g.part = ws;
+    g.kp = a.nkb * 64; g.cpn = a.ncb * 64;
+    const bool wide = p.K > 64;                   // 128-kernel blocks
+    g.nkb = wide ? (a.nkb + 1) / 2 : 1; g.ncb = a.ncb;
+    g.T = int32_t(p.T);
+    g.nsteps = int32_t((p.T + 15) / 16);
+    a.nsplit = g.nsplit = p.wg_fused_ranges;
+    int64_t xs = 1, ys = 1;
+    for (int i = 0; i < 3; ++i) {
+      g.tiles[i] = fast_div(uint32_t(p.tiles[i]));
+      g.X[i] = int32_t(p.X[i]); g.pad[i] = p.pad[i]; g.Y[i] = int32_t(p.Y[i]);
+      xs *= p.X[i]; ys *= p.Y[i];
+    }
+    g.xstride = uint32_t(xs * 4); g.xbytes = uint32_t(xs * 4 * p.C * p.batch);
+    g.ystride = uint32_t(ys * 4); g.ybytes = uint32_t(ys * 4 * p.K * p.batch);
+    const dim3 grid(8 * g.nkb * g.ncb * g.nsplit);
+    if (wide) hipLaunchKernelGGL((k_wgrad_split<128>), grid, dim3(512), 0, s, x, dy, g);
+    else hipLaunchKernelGGL((k_wgrad_split<64>), grid, dim3(512), 0, s, x, dy, g);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3(p.grid_wsum), dim3(256), 0, s, ws, a, int32_t(NXI));
+    hipLaunchKernelGGL((k_wgrad_finish<N, MM, R, CONST>), dim3(p.grid_wfin), dim3(256), 0, s, ws, dw, a, p.fmw);
+    return launch_status();
   }
 
   // Arguments of a pass-accumulating product (k_gemm_acc, k_gemm_acc4): the

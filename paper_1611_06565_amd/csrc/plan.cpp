@@ -209,6 +209,38 @@ void wgrad_geometry(wino_plan_s& p, const SizeTraits& t, const Rat* pts, const R
   p.wgrad_ok = true;
 }
 
+// Whether the weight gradient of an F(2^3, 3^3) layer runs with both transforms
+// inside the product (k_wgrad_split), and over how many tile ranges.  Its
+// window rows and output rows are whole 16-byte units (pad 1 and a multiple of
+// 4 on the last axis), its matrices the default ones, its offsets into x and
+// dy 32-bit with room above the buffers for the masked rows.  The ranges fill
+// the chip with one work-group a compute unit (each costs a partial M, kept
+// where V and D would be).  Measured against the form with V and D in memory
+// (us, here / there): 8 x 64 x 16 x 56 x 56 to 128 kernels 567 / 1069,
+// 8 x 3 x 16 x 56 x 56 to 64 289 / 454, 4 x 256 x 8 x 28 x 28 to 256 298 / 399,
+// 4 x 512 x 2 x 8 x 8 to 512 210 / 224, one channel and kernel 20 / 25: no size
+// was slower.
+void wgrad_split_geometry(wino_plan_s& p, int cus) {
+  p.wg_fused = false;
+  p.wg_fused_ranges = 0;
+  if (!p.wgrad_ok || p.N != 3 || p.kind != 0 || !p.const_mats) return;
+  if (p.pad[2] != 1 || p.X[2] % 4 != 0) return;
+  const int64_t lim = int64_t(1) << 27;             // floats: 2^29 bytes
+  int64_t xn = 0, yn = 0;
+  if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xn) || !mul3_ok(xn, int64_t(p.C), p.batch, &xn) || xn > lim) return;
+  if (!mul3_ok(p.Y[0], p.Y[1], p.Y[2], &yn) || !mul3_ok(yn, int64_t(p.K), p.batch, &yn) || yn > lim) return;
+  const int64_t nkb = cdiv(p.wg_kpad4, 64), ncb = cdiv(p.C_pad, 64);
+  const int64_t blocks = 8 * (p.K > 64 ? cdiv(nkb, 2) : 1) * ncb, steps = cdiv(p.T, 16);
+  int64_t ns = (cus > 0 ? cus : 256) / blocks;
+  const int64_t plane = 64 * nkb * 64 * ncb * 64;   // floats of one range's M
+  const int64_t room = (p.v_floats + p.wg_d_floats + p.wg_part_floats) / plane;
+  ns = ns < steps ? ns : steps;
+  ns = ns < room ? ns : room;
+  if (room < 1 || blocks * ns > kMaxI32) return;
+  p.wg_fused_ranges = int32_t(ns < 1 ? 1 : ns);
+  p.wg_fused = true;
+}
+
 // Growth of fp32 rounding error through the transforms of a point set
 // (§2.2 and §3.3 note that the choice of points trades accuracy): for
 // |g|, |d| <= 1 the first-order error of output i of the 1-D algorithm
@@ -440,6 +472,7 @@ wino_status wino_plan(int N, int m, int r, int C, int K, const int64_t* dims, co
   p.const_mats = defaults;
   fwd_split_geometry(p, uf);
   wgrad_geometry(p, t, pts, R);
+  wgrad_split_geometry(p, device_cu_count());
 
   wino_plan_s* h = new (std::nothrow) wino_plan_s(p);
   if (h == nullptr) return WINO_EINVAL;

@@ -29,6 +29,10 @@ struct wino_plan_s {
   wino::FMats fmw;
   int32_t wg_nsplit, wg_kpad4;
   int64_t wg_d_floats, wg_part_floats;
+  // F(2^3): both of its transforms run inside the product (k_wgrad_split), over
+  // this many tile ranges
+  bool wg_fused;
+  int32_t wg_fused_ranges;
   // pass-accumulating product (m = 2, F(4^2)) tail split, fixed at plan time
   // from the device's compute units: the last xtail[x] blocks of XCD x are
   // done in nparts parts each
