@@ -224,8 +224,9 @@ struct Launch {
       using G = Acc4Geom<N, MM, R>;
       AccArgs a{};
       acc_args(p, a, G::TB, bias, part);
-      if (CONST) {
-        a.nparts = split4_parts<Split4Geom<N, MM, R>>(p);
+      const int np = CONST ? split4_parts<Split4Geom<N, MM, R>>(p) : 0;
+      if (np > 0) {
+        a.nparts = np;
         hipLaunchKernelGGL((k_gemm_split4<N, MM, R>), dim3(p.grid_gemm), dim3(Split4Geom<N, MM, R>::NT), 0, s, V, U,
                            y, a);
       } else {
@@ -291,16 +292,25 @@ struct Launch {
     return int(p.nparts < steps ? p.nparts : steps);
   }
 
-  // Parts of a tail block of k_gemm_split4: the planner's, at most one per two
-  // channel stages, or per stage where fewer than 16 blocks leave the chip
-  // empty anyway (a part costs a whole partial output: 25 blocks of 2 stages
-  // 21 us in two parts, 18 whole; 2 blocks of 4 stages 15 us in four, 17 in two).
+  // Parts of a tail block of k_gemm_split4 (at most the planner's), or 0 where
+  // k_gemm_acc4 is the better one.  A stage of 16 channels takes a block about
+  // 3.4 us, splitting costs a whole partial output per part and the sum's
+  // launch (4 us for a few blocks, 13 for a hundred).  So few blocks are split
+  // down to single stages, and sixteen or more only where that saves at least
+  // six stages: 100 blocks of 4 / 8 / 16 stages take 39 / 45 / 61 us in two
+  // parts and 26 / 40 / 67 whole.  k_gemm_acc4's parts are runs of its 18
+  // passes, so it spreads a block of few stages over more compute units: one
+  // or two blocks of 1 to 6 stages 14 us there, 15 here; 16 to 32 blocks of 5
+  // to 7 stages 25 to 27 there, 27 to 33 here.
   template <class G>
   static int split4_parts(const wino_plan_s& p) {
     const int nstage = p.C_pad / G::SC;
-    int most = p.ntail < 16 ? nstage : nstage / 2;
-    if (most < 1) most = 1;
-    return p.nparts < most ? p.nparts : most;
+    if (p.nparts == 1) return 1;
+    if (p.nparts >= 16 && p.ntail < 4 && nstage < 8) return 0;
+    if (p.nparts >= 8 && p.ntail >= 16 && nstage >= 5 && nstage < 8) return 0;
+    if (p.ntail < 16) return p.nparts < nstage ? p.nparts : nstage;
+    const int np = p.nparts < nstage / 2 ? p.nparts : nstage / 2;
+    return np < 2 || nstage - nstage / np < 6 ? 1 : np;
   }
 
   // Pooled extents of window (2, 2, 2), floor rounding.

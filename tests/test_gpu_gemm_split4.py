@@ -21,6 +21,9 @@ SPECS = [
     layer("half_a_block", 1, 32, 40, (16, 32)),                   # 32 tiles: the block's second half is padding
     layer("past_a_block", 3, 48, 96, (20, 18)),                   # three stages, tiles past one block
     layer("many_parts", 1, 272, 32, (12, 12)),                    # 17 stages in up to 16 uneven parts
+    layer("parts_of_stages", 16, 128, 64, (32, 32)),              # 16 tail blocks of 8 stages in parts
+    layer("few_stages_whole", 24, 32, 32, (30, 31)),              # 24 blocks kept whole
+    layer("passes_instead", 16, 96, 48, (32, 29)),                # 32 blocks of 6 stages: the fp32 passes
     layer("no_padding", 2, 64, 64, (30, 27), pad=0),
 ]
 
