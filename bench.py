@@ -28,6 +28,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA = 157.3      # TFLOP/s, MI355X dense fp32 matrix
+# fp32 operands split into three bf16 each, six bf16 products a term: a sixth of
+# the dense bf16 matrix rate (256 CUs x 4096 FLOP/cycle x 2.4 GHz)
+PEAK_SPLIT = 256 * 4096 * 2.4e9 / 6 / 1e12
 PEAK_HBM = 8000.0           # GB/s, MI355X HBM3E
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 CSRC = "paper_1611_06565_amd/csrc/"
@@ -35,8 +38,8 @@ _COMMON = ["kernels.hpp", "transforms.hpp", "synth.hpp", "layout.hpp", "launch.h
 # the sources that define each kernel family's code (a profile stays valid
 # while they and the plan's launch geometry are unchanged)
 FAMILY_SOURCES = {
-    "m2": _COMMON + ["gemm_acc.hpp", "sizes_m2.hip"],
-    "f42": _COMMON + ["gemm_acc.hpp", "gemm_acc4.hpp", "sizes_f42.hip"],
+    "m2": _COMMON + ["gemm_acc.hpp", "gemm_split.hpp", "sizes_m2.hip"],
+    "f42": _COMMON + ["gemm_acc.hpp", "gemm_acc4.hpp", "gemm_split.hpp", "gemm_split4.hpp", "sizes_f42.hip"],
     "f43": _COMMON + ["sizes_f43.hip"],
     "f43fused": _COMMON + ["fused43.hpp", "fused_f43.hip"],
     "ax": _COMMON + ["aniso.hpp", "sizes_ax.hip"],
@@ -527,12 +530,16 @@ def main():
     y = plan.new_output()
     torch.cuda.synchronize()
 
-    fused = bool(d["fused"])
+    # F(2^3, 3^3) with whole channel groups and 16-byte rows: the forward forms V
+    # inside the product (wino_forward, include/wino.h)
+    split = (spec.N == 3 and list(d["tile"]) == [2, 2, 2] and spec.r == 3 and not args.no_fuse
+             and plan.C % 16 == 0 and d["X"][2] % 4 == 0 and spec.pad == 1)
+    fused = bool(d["fused"]) or split
 
     # One step: kernel transform, input transform, then the batched GEMM with
     # the inverse transform (the two calls wino_forward makes), each timed.
-    # A fused plan (F(4^3), few kernels) runs the last two in one kernel: its
-    # stage is recorded as the GEMM stage and the input stage is empty.
+    # Where the forward runs the last two in one kernel, its stage is recorded
+    # as the GEMM stage and the input stage is empty.
     def step(ev=None):
         if ev is not None:
             ev[0].record()
@@ -544,7 +551,7 @@ def main():
         if ev is not None:
             ev[2].record()
         if fused:
-            plan.forward(xd, U, y=y)
+            plan.forward(xd, U, y=y, workspace=ws)
         else:
             plan.gemm_inverse(ws, U, y)
         if ev is not None:
@@ -599,7 +606,8 @@ def main():
     if fused:
         # the fused kernel reads x (not V), U, and writes y
         gemm_bytes = 4.0 * (float(np.prod(plan.input_shape)) + nxi * C * K + float(np.prod(plan.output_shape)))
-    hbm_bound = gemm_flops / gemm_bytes < PEAK_FP32_MFMA * 1e12 / (PEAK_HBM * 1e9)
+    peak_mfma = PEAK_SPLIT if split or (spec.N, spec.m, spec.r) == (2, 4, 3) else PEAK_FP32_MFMA
+    hbm_bound = gemm_flops / gemm_bytes < peak_mfma * 1e12 / (PEAK_HBM * 1e9)
     if hbm_bound:
         achieved = gemm_bytes / (gemm_ms * 1e-3) / 1e9
     else:
@@ -645,7 +653,7 @@ def main():
             "forward_tflops": flops / ((c_in + c_g) * 1e-3) / 1e12,
             "input_transform_hbm_frac": (in_bytes / (c_in * 1e-3) / 1e9 / PEAK_HBM) if not fused else None,
             "gemm_frac": ((gemm_bytes / (c_g * 1e-3) / 1e9 / PEAK_HBM) if hbm_bound
-                          else (gemm_flops / (c_g * 1e-3) / 1e12 / PEAK_FP32_MFMA)),
+                          else (gemm_flops / (c_g * 1e-3) / 1e12 / peak_mfma)),
             "gemm_bound": "hbm" if hbm_bound else "mfma",
             "flush": "1 GiB device read between repetitions",
         }
@@ -682,7 +690,10 @@ def main():
             "tiles": d["T"], "direct_gflop_per_step": flops / 1e9,
         },
         "roofline": {
-            "kernel": ("k_fused43 (input transform in LDS, batched fp32-MFMA GEMM, fused inverse transform; "
+            "kernel": ("k_split_u + k_fwd_split + k_part_reduce (input transform in LDS, batched GEMM of fp32 operands "
+                       "split into three bf16 on the bf16 matrix cores, fp32 accumulators, fused inverse transform; "
+                       "V never in memory; peak = dense bf16 / 6)" if split else
+                       "k_fused43 (input transform in LDS, batched fp32-MFMA GEMM, fused inverse transform; "
                        "V never in memory)" if fused else
                        "k_gemm_ax (batched fp32-MFMA GEMM, per-axis inverse transform)" if tile else
                        "k_gemm_a8 (batched fp32-MFMA GEMM over each first-axis plane of the 512 elements, "
@@ -693,18 +704,15 @@ def main():
                        if spec.m == 2 and d["gemm_parts"] > 1 else
                        "k_gemm_acc (batched fp32-MFMA GEMM, inverse transform accumulated per pass)"
                        if spec.m == 2 else
-                       "k_gemm_acc4 + k_part_reduce (batched fp32-MFMA GEMM, inverse transform accumulated "
-                       "per pass; the %d tail blocks in %d parts each, their partial outputs summed in order)"
-                       % (d["gemm_tail_blocks"], d["gemm_parts"])
-                       if (spec.N, spec.m, spec.r) == (2, 4, 3) and d["gemm_parts"] > 1 else
-                       "k_gemm_acc4 (batched fp32-MFMA GEMM, inverse transform accumulated per pass)"
+                       "k_gemm_split4 + k_part_reduce (batched GEMM of fp32 operands split into three bf16 on the bf16 "
+                       "matrix cores, fp32 accumulators, fused inverse transform; peak = dense bf16 / 6)"
                        if (spec.N, spec.m, spec.r) == (2, 4, 3) else
                        "k_gemm_inv (batched fp32-MFMA GEMM + fused inverse transform)"),
             "bound": "hbm" if hbm_bound else "mfma",
             "achieved": achieved,
-            "peak": PEAK_HBM if hbm_bound else PEAK_FP32_MFMA,
+            "peak": PEAK_HBM if hbm_bound else peak_mfma,
             "unit": "GB/s" if hbm_bound else "TFLOP/s",
-            "frac": achieved / (PEAK_HBM if hbm_bound else PEAK_FP32_MFMA),
+            "frac": achieved / (PEAK_HBM if hbm_bound else peak_mfma),
             "traffic": traffic,
             "algorithmic": ("4*(alpha^N*T*C + alpha^N*C*K + n*K*prod(Y)) = %.4g bytes per launch" % gemm_bytes
                             if hbm_bound else "2*alpha^N*T*C*K = %.4g FLOP per launch" % gemm_flops),
@@ -712,7 +720,7 @@ def main():
             # MFMA work counted by rocprofv3 (SQ_INSTS_VALU_MFMA_MOPS_F32 x 512)
             # on these kernel sources, and the MFMA fraction it gives here
             "mfma_flops_counted": mfma_counted,
-            "mfma_frac_counted": (mfma_counted / (gemm_ms * 1e-3) / 1e12 / PEAK_FP32_MFMA
+            "mfma_frac_counted": (mfma_counted / (gemm_ms * 1e-3) / 1e12 / peak_mfma
                                   if mfma_counted is not None else None),
         },
         "stages_ms": ({"filter_transform": filt_ms, "fused_forward": gemm_ms} if fused else

@@ -305,6 +305,8 @@ struct Launch {
   template <class G>
   static int split4_parts(const wino_plan_s& p) {
     const int nstage = p.C_pad / G::SC;
+    // a launch holds at most 2^32 - 1 threads (the planner checked 256 a block)
+    if (int64_t(p.grid_gemm) * G::NT > int64_t(0xffffffff)) return 0;
     if (p.nparts == 1) return 1;
     if (p.nparts >= 16 && p.ntail < 4 && nstage < 8) return 0;
     if (p.nparts >= 8 && p.ntail >= 16 && nstage >= 5 && nstage < 8) return 0;

@@ -167,7 +167,8 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   int64_t xs = 0, xn = 0;
   if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xs) || !mul3_ok(xs, int64_t(p.C), p.batch, &xn) || xn > lim) return;
   if (uf / 2 * 3 > p.v_floats) return;
-  if (!grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
+  uint32_t grid = 0;                                // the product's grid at 512 threads
+  if (!grid_ok(p.grid_gemm, 512, &grid) || !grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
   p.fwd_split = true;
 }
 
@@ -236,8 +237,10 @@ void wgrad_split_geometry(wino_plan_s& p, int cus) {
   const int64_t room = (p.v_floats + p.wg_d_floats + p.wg_part_floats) / plane;
   ns = ns < steps ? ns : steps;
   ns = ns < room ? ns : room;
-  if (room < 1 || blocks * ns > kMaxI32) return;
-  p.wg_fused_ranges = int32_t(ns < 1 ? 1 : ns);
+  uint32_t grid = 0;
+  ns = ns < 1 ? 1 : ns;
+  if (room < 1 || !grid_ok(blocks * ns, 512, &grid)) return;
+  p.wg_fused_ranges = int32_t(ns);
   p.wg_fused = true;
 }
 
