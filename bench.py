@@ -533,7 +533,8 @@ def main():
     # F(2^3, 3^3) with whole channel groups and 16-byte rows: the forward forms V
     # inside the product (wino_forward, include/wino.h)
     split = (spec.N == 3 and list(d["tile"]) == [2, 2, 2] and spec.r == 3 and not args.no_fuse
-             and plan.C % 16 == 0 and d["X"][2] % 4 == 0 and spec.pad == 1)
+             and plan.C % 16 == 0 and d["X"][2] % 4 == 0 and spec.pad == 1
+             and d["T_pad"] >= (2 if d["T_pad"] >= 512 else 3) * d["K_pad"])
     fused = bool(d["fused"]) or split
 
     # One step: kernel transform, input transform, then the batched GEMM with

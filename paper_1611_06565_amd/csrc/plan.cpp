@@ -158,7 +158,10 @@ bool acc_geometry(wino_plan_s& p, const SizeTraits& t, bool split, int cus) {
 // the split kernels (three bf16 for each of U's floats) take V's place in the
 // workspace.  Everything else runs in two stages.  Measured both ways (us, one
 // stage against two): 8 x 64 x 16 x 56 x 56 to 128 kernels 535 / 685, its data
-// gradient (128 to 64) 530 / 858.
+// gradient (128 to 64) 530 / 858, 1 x 16 x 8 x 16 x 16 to 16 18 / 22.  With few
+// tiles a kernel the splitting of U outweighs V's traffic: 256 channels to 256
+// kernels with 448 tiles (1.75 a kernel) 59 / 58, with 576 82 / 90; 64 to 128
+// with 320 tiles 31.3 / 30.8, with 448 31 / 32.
 void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   p.fwd_split = false;
   if (p.N != 3 || p.kind != 0 || !p.const_mats || (p.flags & WINO_NO_FUSE)) return;
@@ -166,7 +169,8 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   const int64_t lim = int64_t(1) << 27;             // floats of x: 2^29 bytes
   int64_t xs = 0, xn = 0;
   if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xs) || !mul3_ok(xs, int64_t(p.C), p.batch, &xn) || xn > lim) return;
-  if (uf / 2 * 3 > p.v_floats) return;
+  const int64_t tk = p.T_pad / p.K_pad;             // (the split kernels take 3/2 of U)
+  if (tk < 2 || (tk < 3 && p.T_pad < 512)) return;
   uint32_t grid = 0;                                // the product's grid at 512 threads
   if (!grid_ok(p.grid_gemm, 512, &grid) || !grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
   p.fwd_split = true;

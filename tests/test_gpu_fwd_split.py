@@ -18,18 +18,20 @@ def layer(name, batch, C, K, X, pad=1, **kw):
 
 
 INSIDE = [
-    layer("one_pair_of_tiles", 1, 16, 1, (1, 1, 4)),              # smallest: two tiles, one kernel, one stage
-    layer("odd_first_axes", 2, 32, 70, (3, 5, 8), relu=True),     # cropped tiles, ragged kernel block
+    layer("three_tiles_a_kernel", 1, 16, 1, (2, 16, 40)),          # 160 tiles (192 padded) for 64 kernels, one stage
+    layer("odd_first_axes", 2, 32, 70, (7, 11, 36), relu=True),   # cropped tiles, ragged kernel block
     layer("ragged_tile_block", 3, 48, 64, (5, 7, 12), leaky=0.2),  # T past a whole block, three stages
-    layer("rows_of_33_tiles", 1, 16, 130, (4, 6, 132)),           # rows longer than a wave's 32 tiles
-    layer("rows_of_32_tiles", 2, 64, 128, (4, 4, 64)),            # rows end where the wave's tiles do
+    layer("rows_of_66_tiles", 1, 16, 130, (8, 6, 132)),           # rows longer than a wave's 32 tiles
+    layer("rows_of_32_tiles", 2, 64, 128, (4, 8, 64)),            # rows end where the wave's tiles do
+    layer("rows_of_2_tiles", 5, 16, 3, (9, 13, 4)),               # every pair of tiles is a row
     layer("whole_blocks", 8, 32, 64, (16, 56, 56)),               # full rounds and a split tail
 ]
 OUTSIDE = [
-    layer("row_not_of_4", 2, 32, 70, (3, 5, 10)),
-    layer("channels_not_of_16", 2, 24, 64, (4, 6, 8)),
-    layer("no_padding", 2, 32, 64, (6, 7, 8), pad=0),
-    layer("kernels_split_larger_than_v", 1, 16, 400, (2, 4, 8)),
+    layer("row_not_of_4", 2, 32, 64, (7, 11, 34)),
+    layer("channels_not_of_16", 1, 24, 64, (8, 12, 32)),
+    layer("no_padding", 2, 32, 64, (10, 12, 36), pad=0),
+    layer("few_tiles_a_kernel", 1, 16, 400, (2, 4, 8)),
+    layer("one_pair_of_tiles", 1, 16, 1, (1, 1, 4)),
 ]
 
 
@@ -49,9 +51,9 @@ def test_pads_of_the_leading_axes():
     from oracle.direct import direct_blas
     from oracle.metric import normalised_error
     from paper_1611_06565_amd.wino import Plan
-    spec = layer("pads_0_2_1", 2, 32, 64, (6, 5, 8))
+    spec = layer("pads_0_2_1", 2, 32, 64, (6, 9, 32))
     x, w = draw_layer(spec, seed=5)
-    plan = Plan(3, 2, 3, 32, 64, [2, 6, 5, 8], pad=[0, 2, 1])
+    plan = Plan(3, 2, 3, 32, 64, [2, 6, 9, 32], pad=[0, 2, 1])
     y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda())).cpu().numpy()
     xp = np.pad(x, ((0, 0), (0, 0), (0, 0), (2, 2), (1, 1)))
     ref, den = direct_blas(xp, w, 0)
@@ -65,12 +67,12 @@ def test_error_no_larger_than_two_stages():
     from oracle.direct import direct_blas
     from paper_1611_06565_amd.wino import Plan
     for C, dist in ((16, "normal"), (64, "relu_normal"), (256, "uniform")):
-        spec = layer("err", 1, C, 64, (6, 8, 16)).with_(x_dist=dist)
+        spec = layer("err", 2, C, 64, (6, 8, 32)).with_(x_dist=dist)
         x, w = draw_layer(spec, seed=9)
         ref, _ = direct_blas(x, w, 1)
         err = []
         for fuse in (True, False):
-            plan = Plan(3, 2, 3, C, 64, [1, 6, 8, 16], pad=1, fuse=fuse)
+            plan = Plan(3, 2, 3, C, 64, [2, 6, 8, 32], pad=1, fuse=fuse)
             y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda()))
             err.append(np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref))
         print(C, dist, err)
