@@ -114,11 +114,16 @@ typedef struct {
   int32_t default_points;/* 1 when the transform constants are compiled in        */
   int32_t channel_group; /* CG: channels interleaved innermost in V                 */
   int32_t filter_channel_group; /* CGU: channels interleaved innermost in U        */
-  int32_t gemm_parts;    /* parts each tail block of the product is split into   */
-  int64_t gemm_tail_blocks; /* product blocks split into gemm_parts parts         */
+  int32_t gemm_parts;    /* parts wino_gemm_inverse splits each tail block into (1: none) */
+  int64_t gemm_tail_blocks; /* product blocks it splits so (0 when gemm_parts is 1) */
   int32_t fused;         /* 1: wino_forward fuses the input transform into the product */
   int32_t tile[3];       /* output-tile extent per axis (1 past N)                */
   int32_t alpha_axis[3]; /* input-tile extent per axis, tile + r - 1 (1 past N)   */
+  int32_t gemm_split;    /* 1: wino_gemm_inverse multiplies split operands (F(4^2, 3^2)) */
+  int32_t forward_split; /* 1: wino_forward of an F(2^3, 3^3) layer is the one-kernel form */
+  int32_t forward_parts; /* parts wino_forward splits each tail block into (1: none) */
+  int32_t wgrad_split;   /* 1: wino_weight_gradient forms both transforms inside its product */
+  int32_t wgrad_ranges;  /* tile ranges of its partial products (0: no weight gradient) */
 } wino_plan_desc;
 
 /* Build a plan for one layer.  §3.1-§3.3 and §4.1.
@@ -168,10 +173,12 @@ size_t wino_filter_bytes(const wino_plan_t* plan);
  * (xi, c, t) sits at (((t/B)*C_pad/CG + c/CG)*alpha^N + xi)*B*CG + (t%B)*CG
  * + c%CG.  For F(2^N, 3^N) and F(4^2, 3^2) the product's blocks (64 tiles x 64
  * or 32 kernels) that would run in a last, partly filled round of resident
- * work-groups on the device current at wino_plan (gemm_tail_blocks) are split
- * by element passes into gemm_parts work-groups each, and a scratch area for
- * their partial outputs follows V (at V's size rounded up to 256 bytes);
- * wino_gemm_inverse overwrites it.
+ * work-groups on the device current at wino_plan (gemm_tail_blocks) can be
+ * split into several work-groups each, by element passes or, where gemm_split
+ * or forward_split is 1, by channels (gemm_parts and forward_parts say into
+ * how many), and a scratch area for their partial outputs, sized for the
+ * finest of these splits, follows V (at V's size rounded up to 256 bytes);
+ * wino_gemm_inverse and wino_forward overwrite it.
  * The split is fixed when the plan is made and the partials are summed in a
  * fixed order, so a plan's results are bitwise reproducible. */
 size_t wino_workspace_bytes(const wino_plan_t* plan);

@@ -224,9 +224,8 @@ struct Launch {
       using G = Acc4Geom<N, MM, R>;
       AccArgs a{};
       acc_args(p, a, G::TB, bias, part);
-      const int np = CONST ? split4_parts<Split4Geom<N, MM, R>>(p) : 0;
-      if (np > 0) {
-        a.nparts = np;
+      if (CONST && p.split4_parts > 0) {
+        a.nparts = p.split4_parts;
         hipLaunchKernelGGL((k_gemm_split4<N, MM, R>), dim3(p.grid_gemm), dim3(Split4Geom<N, MM, R>::NT), 0, s, V, U,
                            y, a);
       } else {
@@ -257,7 +256,7 @@ struct Launch {
       hipLaunchKernelGGL(k_split_u, dim3(p.grid_split_u), dim3(256), 0, s, U, P, n8, int32_t(p.K_pad));
       FuseArgs a{};
       acc_args(p, a.g, G::TB, bias, ws + p.v_floats);
-      a.g.nparts = split_parts<G>(p);
+      a.g.nparts = p.fwd_parts;
       a.C = p.C;
       int64_t xs = 1;
       for (int i = 0; i < 3; ++i) {
@@ -282,37 +281,6 @@ struct Launch {
     } else {
       return WINO_EUNSUPPORTED;
     }
-  }
-
-  // Parts of a tail block of the split product: the planner's, at most one
-  // per (pass, channel stage) step.
-  template <class G>
-  static int split_parts(const wino_plan_s& p) {
-    const int64_t steps = int64_t(G::NPASS) * (p.C_pad / G::SC);
-    return int(p.nparts < steps ? p.nparts : steps);
-  }
-
-  // Parts of a tail block of k_gemm_split4 (at most the planner's), or 0 where
-  // k_gemm_acc4 is the better one.  A stage of 16 channels takes a block about
-  // 3.4 us, splitting costs a whole partial output per part and the sum's
-  // launch (4 us for a few blocks, 13 for a hundred).  So few blocks are split
-  // down to single stages, and sixteen or more only where that saves at least
-  // six stages: 100 blocks of 4 / 8 / 16 stages take 39 / 45 / 61 us in two
-  // parts and 26 / 40 / 67 whole.  k_gemm_acc4's parts are runs of its 18
-  // passes, so it spreads a block of few stages over more compute units: one
-  // or two blocks of 1 to 6 stages 14 us there, 15 here; 16 to 32 blocks of 5
-  // to 7 stages 25 to 27 there, 27 to 33 here.
-  template <class G>
-  static int split4_parts(const wino_plan_s& p) {
-    const int nstage = p.C_pad / G::SC;
-    // a launch holds at most 2^32 - 1 threads (the planner checked 256 a block)
-    if (int64_t(p.grid_gemm) * G::NT > int64_t(0xffffffff)) return 0;
-    if (p.nparts == 1) return 1;
-    if (p.nparts >= 16 && p.ntail < 4 && nstage < 8) return 0;
-    if (p.nparts >= 8 && p.ntail >= 16 && nstage >= 5 && nstage < 8) return 0;
-    if (p.ntail < 16) return p.nparts < nstage ? p.nparts : nstage;
-    const int np = p.nparts < nstage / 2 ? p.nparts : nstage / 2;
-    return np < 2 || nstage - nstage / np < 6 ? 1 : np;
   }
 
   // Pooled extents of window (2, 2, 2), floor rounding.

@@ -164,6 +164,7 @@ bool acc_geometry(wino_plan_s& p, const SizeTraits& t, bool split, int cus) {
 // with 320 tiles 31.3 / 30.8, with 448 31 / 32.
 void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   p.fwd_split = false;
+  p.fwd_parts = 0;
   if (p.N != 3 || p.kind != 0 || !p.const_mats || (p.flags & WINO_NO_FUSE)) return;
   if (p.pad[2] != 1 || p.X[2] % 4 != 0 || p.C % 16 != 0) return;
   const int64_t lim = int64_t(1) << 27;             // floats of x: 2^29 bytes
@@ -173,7 +174,32 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   if (tk < 2 || (tk < 3 && p.T_pad < 512)) return;
   uint32_t grid = 0;                                // the product's grid at 512 threads
   if (!grid_ok(p.grid_gemm, 512, &grid) || !grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
+  const int64_t units = int64_t(p.nxi / 8) * (p.C_pad / 16);   // (pass of eight elements, channel stage) steps
+  p.fwd_parts = int32_t(p.nparts < units ? p.nparts : units);
   p.fwd_split = true;
+}
+
+// Parts of a tail block of k_gemm_split4 (at most the planner's), or 0 where
+// k_gemm_acc4 is the better one.  A stage of 16 channels takes a block about
+// 3.4 us, splitting costs a whole partial output per part and the sum's
+// launch (4 us for a few blocks, 13 for a hundred).  So few blocks are split
+// down to single stages, and sixteen or more only where that saves at least
+// six stages: 100 blocks of 4 / 8 / 16 stages take 39 / 45 / 61 us in two
+// parts and 26 / 40 / 67 whole.  k_gemm_acc4's parts are runs of its 18
+// passes, so it spreads a block of few stages over more compute units: one
+// or two blocks of 1 to 6 stages 14 us there, 15 here; 16 to 32 blocks of 5
+// to 7 stages 25 to 27 there, 27 to 33 here.
+void split4_geometry(wino_plan_s& p) {
+  p.split4_parts = 0;
+  uint32_t grid = 0;                                // the product's grid at 768 threads
+  if (p.kind != 1 || !p.const_mats || !grid_ok(p.grid_gemm, 768, &grid)) return;
+  const int nstage = p.C_pad / 16;
+  if (p.nparts == 1) { p.split4_parts = 1; return; }
+  if (p.nparts >= 16 && p.ntail < 4 && nstage < 8) return;
+  if (p.nparts >= 8 && p.ntail >= 16 && nstage >= 5 && nstage < 8) return;
+  if (p.ntail < 16) { p.split4_parts = p.nparts < nstage ? p.nparts : nstage; return; }
+  const int np = p.nparts < nstage / 2 ? p.nparts : nstage / 2;
+  p.split4_parts = np < 2 || nstage - nstage / np < 6 ? 1 : np;
 }
 
 // Weight-gradient geometry (F(r, m) on the forward's points, V reused): the
@@ -478,6 +504,7 @@ wino_status wino_plan(int N, int m, int r, int C, int K, const int64_t* dims, co
   p.fm = to_fmats(R);
   p.const_mats = defaults;
   fwd_split_geometry(p, uf);
+  split4_geometry(p);
   wgrad_geometry(p, t, pts, R);
   wgrad_split_geometry(p, device_cu_count());
 
@@ -501,11 +528,17 @@ wino_status wino_plan_describe(const wino_plan_t* p, wino_plan_desc* d) {
   d->block_kernels = p->kblk;
   d->channel_group = p->cg;
   d->filter_channel_group = p->cgu;
-  d->gemm_parts = p->nparts;
-  d->gemm_tail_blocks = p->ntail;
+  const int32_t parts = p->split4_parts > 0 ? p->split4_parts : p->nparts;
+  d->gemm_parts = parts;
+  d->gemm_tail_blocks = parts > 1 ? p->ntail : 0;
   d->default_points = p->const_mats ? 1 : 0;
   d->fused = p->fused ? 1 : 0;
   for (int i = 0; i < 3; ++i) { d->tile[i] = p->mv[i]; d->alpha_axis[i] = p->av[i]; }
+  d->gemm_split = p->split4_parts > 0 ? 1 : 0;
+  d->forward_split = p->fwd_split ? 1 : 0;
+  d->forward_parts = p->fwd_split ? p->fwd_parts : (p->fused ? 1 : parts);
+  d->wgrad_split = p->wg_fused ? 1 : 0;
+  d->wgrad_ranges = p->wg_fused ? p->wg_fused_ranges : (p->wgrad_ok ? p->wg_nsplit : 0);
   return WINO_OK;
 }
 

@@ -39,6 +39,11 @@ struct wino_plan_s {
   int nparts;             // 1: no split
   int32_t xtail[8];
   int64_t ntail;          // sum of xtail
+  // the same split as the kernels on the bf16 matrix cores run it (at most
+  // nparts parts): parts of a tail block of k_gemm_split4 (F(4^2); 0: the
+  // product runs on k_gemm_acc4 instead) and of k_fwd_split (F(2^3) with
+  // fwd_split; 0 otherwise)
+  int32_t split4_parts, fwd_parts;
   int64_t v_floats;       // V in the workspace (rounded up to 256 bytes)
   int64_t part_floats;    // partial outputs after V when nparts > 1
   uint32_t flags;

@@ -49,7 +49,10 @@ class _Desc(ctypes.Structure):
                 ("default_points", ctypes.c_int32), ("channel_group", ctypes.c_int32),
                 ("filter_channel_group", ctypes.c_int32), ("gemm_parts", ctypes.c_int32),
                 ("gemm_tail_blocks", ctypes.c_int64), ("fused", ctypes.c_int32),
-                ("tile", ctypes.c_int32 * 3), ("alpha_axis", ctypes.c_int32 * 3)]
+                ("tile", ctypes.c_int32 * 3), ("alpha_axis", ctypes.c_int32 * 3),
+                ("gemm_split", ctypes.c_int32), ("forward_split", ctypes.c_int32),
+                ("forward_parts", ctypes.c_int32), ("wgrad_split", ctypes.c_int32),
+                ("wgrad_ranges", ctypes.c_int32)]
 
 
 _LIB = None

@@ -165,6 +165,58 @@ int main() {
     o.tile[0] = 2; o.tile[1] = 4; o.tile[2] = 4;
     CHECK(wino_plan(3, 4, 3, 4, 4, big, &o, &p) == WINO_EINVAL, "per-axis tiles, tiles past 2^31");
   }
+  // wino_plan_describe names the kernels that run: the split products
+  {
+    const int64_t d3[4] = {8, 16, 56, 56}, odd[4] = {8, 16, 56, 54}, d2[3] = {64, 56, 56}, one[3] = {1, 8, 8};
+    wino_plan_t* p = nullptr;
+    wino_plan_desc d{};
+    CHECK(plan_status(3, 2, 3, 64, 128, d3, 1, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK, "F(2^3) layer");
+    CHECK(d.forward_split == 1 && d.forward_parts == 8 && d.wgrad_split == 1 && d.wgrad_ranges == 32 &&
+              d.gemm_split == 0 && d.fused == 0,
+          "F(2^3): forward and weight gradient on the split products");
+    wino_destroy(p);
+    CHECK(plan_status(3, 2, 3, 16, 64, d3, 1, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.gemm_parts >= d.forward_parts && d.forward_parts <= 8,
+          "F(2^3), one stage: at most eight parts in the forward");
+    wino_destroy(p);
+    CHECK(plan_status(3, 2, 3, 64, 128, odd, 1, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.forward_split == 0 && d.wgrad_split == 0 && d.wgrad_ranges >= 1 && d.forward_parts == d.gemm_parts,
+          "F(2^3), rows not a multiple of 4: the fp32 products");
+    wino_destroy(p);
+    wino_opts o{};
+    o.pad[0] = o.pad[1] = o.pad[2] = 1;
+    o.flags = WINO_NO_FUSE;
+    p = nullptr;
+    CHECK(wino_plan(3, 2, 3, 64, 128, d3, &o, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.forward_split == 0 && d.forward_parts == d.gemm_parts && d.wgrad_split == 1,
+          "F(2^3), WINO_NO_FUSE: the forward in two stages");
+    wino_destroy(p);
+    p = nullptr;
+    CHECK(plan_status(2, 4, 3, 256, 256, d2, 1, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.gemm_split == 1 && d.gemm_tail_blocks == 32 && d.gemm_parts > 1 && d.forward_parts == d.gemm_parts,
+          "F(4^2): split product, tail blocks in parts of channels");
+    wino_destroy(p);
+    const double pts[5] = {0.0, 1.0, -1.0, 1.0 / 3.0, -1.0 / 3.0};
+    o = wino_opts{};
+    o.points = pts;
+    o.n_points = 5;
+    p = nullptr;
+    CHECK(wino_plan(2, 4, 3, 256, 256, d2, &o, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.gemm_split == 0 && d.gemm_parts == 8,
+          "F(4^2), caller's points: the fp32 passes");
+    wino_destroy(p);
+    // the numbers reported are those of the launch: no part without a channel stage of its own
+    for (int C = 1; C <= 600; C += 7) {
+      p = nullptr;
+      if (plan_status(2, 4, 3, C, 40, one, 1, &p) != WINO_OK || wino_plan_describe(p, &d) != WINO_OK) std::abort();
+      if (d.gemm_split == 1 && (d.gemm_parts > (C + 15) / 16 || (d.gemm_parts == 1) != (d.gemm_tail_blocks == 0))) {
+        std::fprintf(stderr, "FAIL: C = %d: %d parts, %lld blocks\n", C, d.gemm_parts, (long long)d.gemm_tail_blocks);
+        return 1;
+      }
+      wino_destroy(p);
+    }
+    std::printf("ok: F(4^2) parts against channel stages\n");
+  }
   // max-pool geometry
   {
     using wino::PoolGeom;

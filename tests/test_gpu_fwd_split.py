@@ -40,7 +40,8 @@ OUTSIDE = [
 def test_full_output(spec, split):
     x, w = draw_layer(spec, seed=41)
     b = (np.random.default_rng(2).standard_normal(spec.K) * 0.3).astype(np.float32)
-    y, _ = run_layer(spec, x, w, bias=b, guard=1024, split=split)
+    y, plan = run_layer(spec, x, w, bias=b, guard=1024, split=split)
+    assert plan.desc["forward_split"] == (spec in INSIDE), plan.desc
     check_full(spec, y, x, w, bias=b)
 
 
@@ -54,6 +55,7 @@ def test_pads_of_the_leading_axes():
     spec = layer("pads_0_2_1", 2, 32, 64, (6, 9, 32))
     x, w = draw_layer(spec, seed=5)
     plan = Plan(3, 2, 3, 32, 64, [2, 6, 9, 32], pad=[0, 2, 1])
+    assert plan.desc["forward_split"] == 1
     y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda())).cpu().numpy()
     xp = np.pad(x, ((0, 0), (0, 0), (0, 0), (2, 2), (1, 1)))
     ref, den = direct_blas(xp, w, 0)
@@ -73,6 +75,7 @@ def test_error_no_larger_than_two_stages():
         err = []
         for fuse in (True, False):
             plan = Plan(3, 2, 3, C, 64, [2, 6, 8, 32], pad=1, fuse=fuse)
+            assert plan.desc["forward_split"] == fuse
             y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda()))
             err.append(np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref))
         print(C, dist, err)

@@ -28,10 +28,15 @@ SPECS = [
 ]
 
 
+# layers whose blocks the fp32 passes spread further (not with WINO_NO_SPLIT)
+PASSES = ("one_output", "rows_of_whole_units", "ragged_rows", "half_a_block", "passes_instead")
+
+
 @pytest.mark.parametrize("split", [True, False], ids=["parts", "whole"])
 @pytest.mark.parametrize("spec", SPECS, ids=lambda s: s.name)
 def test_full_output(spec, split):
     x, w = draw_layer(spec, seed=17)
     b = (np.random.default_rng(4).standard_normal(spec.K) * 0.3).astype(np.float32)
-    y, _ = run_layer(spec, x, w, bias=b, guard=1024, split=split)
+    y, plan = run_layer(spec, x, w, bias=b, guard=1024, split=split)
+    assert plan.desc["gemm_split"] == (0 if split and spec.name in PASSES else 1), plan.desc
     check_full(spec, y, x, w, bias=b)

@@ -35,6 +35,7 @@ def test_full_output(layer):
     name, batch, C, K, X = layer
     rng = np.random.default_rng(8)
     plan = Plan(3, 2, 3, C, K, [batch, *X], pad=1)
+    assert plan.desc["wgrad_split"] == 1, plan.desc
     x = rng.standard_normal(plan.input_shape, dtype=np.float32)
     dy = rng.standard_normal(plan.output_shape, dtype=np.float32)
     n = int(np.prod(plan.weight_shape))
@@ -55,6 +56,7 @@ def test_leading_pads():
     from paper_1611_06565_amd.wino import Plan
     rng = np.random.default_rng(3)
     plan = Plan(3, 2, 3, 9, 10, [2, 6, 5, 8], pad=[0, 2, 1])
+    assert plan.desc["wgrad_split"] == 1, plan.desc
     x = rng.standard_normal(plan.input_shape, dtype=np.float32)
     dy = rng.standard_normal(plan.output_shape, dtype=np.float32)
     dw = plan.weight_gradient(torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()).cpu().numpy()
