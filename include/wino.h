@@ -256,10 +256,11 @@ wino_status wino_transform_filter_adjoint(const wino_plan_t* plan, const float* 
  *   dw         device, [K][C][r^N] float32, fully overwritten
  *   workspace  device, wino_weight_gradient_workspace_bytes(plan) bytes: V,
  *              then the transformed dy and the partial products of the
- *              tile ranges (all overwritten); F(2^3, 3^3) plans with the
- *              default points, pad 1 and a multiple of 4 along the last axis
- *              (x and dy at most 512 MiB each) form both transforms inside
- *              the product and keep only the partial products in it
+ *              tile ranges (all overwritten); plans with desc.wgrad_split = 1
+ *              (F(2^3, 3^3) with the default points, pad 1 and a multiple of
+ *              4 along the last axis, at least eight tiles, x and dy at most
+ *              512 MiB each) form both transforms inside the product and keep
+ *              only the partial products in it
  * The partial products are summed in a fixed order: results are bitwise
  * reproducible for a plan. */
 size_t wino_weight_gradient_workspace_bytes(const wino_plan_t* plan);

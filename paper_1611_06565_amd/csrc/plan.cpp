@@ -244,18 +244,29 @@ void wgrad_geometry(wino_plan_s& p, const SizeTraits& t, const Rat* pts, const R
 // inside the product (k_wgrad_split), and over how many tile ranges.  Its
 // window rows and output rows are whole 16-byte units (pad 1 and a multiple of
 // 4 on the last axis), its matrices the default ones, its offsets into x and
-// dy 32-bit with room above the buffers for the masked rows.  The ranges fill
+// dy 32-bit with room above the buffers for the masked rows.  Two kinds of
+// layers keep the fp32 products: fewer than eight tiles, where the terms that
+// the split leaves out weigh more than the roundings it saves (2-norm error
+// against the fp32 form's over 48 x 48 channel pairs: 1.06 to 1.23 with two
+// tiles, 1.00 to 1.07 with four, 0.90 with eight, 0.79 with sixteen); and a
+// leading axis of one position inside its padding, where the outer taps sum
+// nothing and their exact zeros show what is left of products that cancel
+// (normalised error 0.8e-4 to 1.3e-4 against 0.5e-4 to 0.8e-4 on 1 x 28 x 28
+// and 28 x 1 x 28, with the library's bar at 1e-4).  The ranges fill
 // the chip with one work-group a compute unit (each costs a partial M, kept
 // where V and D would be).  Measured against the form with V and D in memory
 // (us, here / there): 8 x 64 x 16 x 56 x 56 to 128 kernels 567 / 1069,
 // 8 x 3 x 16 x 56 x 56 to 64 289 / 454, 4 x 256 x 8 x 28 x 28 to 256 298 / 399,
 // 4 x 512 x 2 x 8 x 8 to 512 210 / 224, one channel and kernel 20 / 25: no size
-// was slower.
+// of these was slower.
 void wgrad_split_geometry(wino_plan_s& p, int cus) {
   p.wg_fused = false;
   p.wg_fused_ranges = 0;
   if (!p.wgrad_ok || p.N != 3 || p.kind != 0 || !p.const_mats) return;
   if (p.pad[2] != 1 || p.X[2] % 4 != 0) return;
+  if (p.T < 8) return;
+  for (int i = 0; i < 2; ++i)
+    if (p.X[i] == 1 && p.pad[i] == 1) return;
   const int64_t lim = int64_t(1) << 27;             // floats: 2^29 bytes
   int64_t xn = 0, yn = 0;
   if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xn) || !mul3_ok(xn, int64_t(p.C), p.batch, &xn) || xn > lim) return;

@@ -205,6 +205,21 @@ int main() {
               d.gemm_split == 0 && d.gemm_parts == 8,
           "F(4^2), caller's points: the fp32 passes");
     wino_destroy(p);
+    const int64_t thin[4] = {2, 1, 16, 16}, flat[4] = {2, 16, 1, 16}, few[4] = {1, 2, 2, 12}, some[4] = {1, 2, 2, 16},
+                  wide[4] = {1, 1, 16, 16};
+    const int64_t* ds[4] = {thin, flat, few, some};
+    for (int i = 0; i < 4; ++i) {
+      p = nullptr;
+      if (plan_status(3, 2, 3, 8, 8, ds[i], 1, &p) != WINO_OK || wino_plan_describe(p, &d) != WINO_OK) std::abort();
+      CHECK(d.wgrad_split == (i == 3), "weight gradient of thin and short layers on the fp32 products");
+      wino_destroy(p);
+    }
+    o = wino_opts{};
+    o.pad[0] = 2; o.pad[1] = o.pad[2] = 1;
+    p = nullptr;
+    CHECK(wino_plan(3, 2, 3, 8, 8, wide, &o, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK && d.wgrad_split == 1,
+          "one position with two of padding: every tap sums something");
+    wino_destroy(p);
     // the numbers reported are those of the launch: no part without a channel stage of its own
     for (int C = 1; C <= 600; C += 7) {
       p = nullptr;
