@@ -119,7 +119,8 @@ typedef struct {
   int32_t fused;         /* 1: wino_forward fuses the input transform into the product */
   int32_t tile[3];       /* output-tile extent per axis (1 past N)                */
   int32_t alpha_axis[3]; /* input-tile extent per axis, tile + r - 1 (1 past N)   */
-  int32_t gemm_split;    /* 1: wino_gemm_inverse multiplies split operands (F(4^2, 3^2)) */
+  int32_t gemm_split;    /* F(4^2, 3^2), wino_gemm_inverse: 1 multiplies split operands, 2 the
+                          * same kernel in fp32 (at most four channels), 0 the fp32 passes */
   int32_t forward_split; /* 1: wino_forward of an F(2^3, 3^3) layer is the one-kernel form */
   int32_t forward_parts; /* parts wino_forward splits each tail block into (1: none) */
   int32_t wgrad_split;   /* 1: wino_weight_gradient forms both transforms inside its product */

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "gemm_acc.hpp"
 #include "gemm_split.hpp"
@@ -30,6 +31,38 @@ struct Split4Geom {
   static_assert(MM * KB * LDK <= NXI * HT * KB, "the stitch fits the exchange");
 };
 
+// out[o * os] = sum_i AT[o][i] v[i * vs] of the default points, the terms in
+// pairs (0, 1), (2, 3), .. added in order.  The sums and differences that the
+// columns of points a and -a share (apply_vec) take 10 operations for F(4, 3)
+// instead of 14, but round more: on one channel's products (float64 beside
+// them) they leave a relative error of 3.3e-7, this 2.6e-7 and k_gemm_acc4's
+// running sum 2.7e-7.  Over many channels that is below the products' own
+// rounding, and the 4 operations are 0.5% of a layer's time.
+template <int MM, int R>
+__device__ __forceinline__ void at_pairs(const float* v, int vs, float* out, int os) {
+  constexpr int A = MM + R - 1;
+  unroll<MM>([&](auto O) {
+    constexpr int o = decltype(O)::value;
+    float sum = 0.0f;
+    bool any = false;                             // folds away: every entry is a constant
+    unroll<A / 2>([&](auto P) {
+      constexpr float c0 = const_entry<Which::AT, MM, R>(o, 2 * decltype(P)::value);
+      constexpr float c1 = const_entry<Which::AT, MM, R>(o, 2 * decltype(P)::value + 1);
+      const float v0 = v[2 * decltype(P)::value * vs], v1 = v[(2 * decltype(P)::value + 1) * vs];
+      if constexpr (c0 == 0.0f && c1 == 0.0f) return;
+      else {
+        float pair;
+        if constexpr (c1 == 0.0f) pair = c0 * v0;
+        else if constexpr (c0 == 0.0f) pair = c1 * v1;
+        else pair = __builtin_fmaf(c1, v1, c0 * v0);
+        sum = any ? sum + pair : pair;
+        any = true;
+      }
+    });
+    out[o * os] = sum;
+  });
+}
+
 // One work-group: 64 tiles x 32 kernels, twelve waves; wave w owns elements
 // 3w .. 3w + 2 (96 accumulators), so every V and U value of the block is
 // loaded and split by exactly one wave, straight from global memory to
@@ -38,6 +71,15 @@ struct Split4Geom {
 // products of 32 tiles at a time meet in LDS (144 KB), a thread applies A^T to
 // two (tile, kernel) pairs, and the outputs go through LDS once more so that
 // neighbouring lanes store neighbouring tiles' rows, 16 bytes each.
+//
+// FEW (at most four channels): one channel group, lane half h takes channels
+// 2h and 2h + 1 and multiplies them in fp32 (two k-steps an element).  The
+// terms that the split leaves out weigh more there than the roundings it saves:
+// against float64 (2-norm, 2 x C x 48 x 64, K = 64) the split products show
+// 1.18, 1.12, 1.07 and 1.04 times k_gemm_acc4's error for 1 to 4 channels, 1.00
+// for 5, 0.97 for 6 and 0.77 for 16; FEW, with at_pairs, 0.98 to 1.00.  FEW also
+// has no splits to make: the forward of 32 x 3 x 224 x 224, K = 64, 248 -> 229
+// us, k_gemm_acc4's 300.
 //
 // What bounds it: the sum of its parts, which hardly overlap (on 64 x 256 x
 // 56 x 56, K = 256, 535-575 us: matrix work 200 at the clock it falls to, the
@@ -50,7 +92,7 @@ struct Split4Geom {
 // blocks of a tile block re-read it (570 -> 531 us against non-temporal loads;
 // the next input transform then finds less of x in the memory-side cache and
 // gives the 40 us back where x is the same tensor each time).
-template <int N, int MM, int R>
+template <int N, int MM, int R, bool FEW>
 __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict__ V, const float* __restrict__ U,
                                                         float* __restrict__ y, AccArgs g) {
   using G = Split4Geom<N, MM, R>;
@@ -81,22 +123,25 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
 
   constexpr int64_t VX = TB * 4, VG = int64_t(NXI) * TB * 4;      // V element / group strides (floats)
   const int64_t UG = int64_t(g.K_pad) * 4;                        // U group stride
-  const uint32_t vlane = uint32_t(half) * uint32_t(2 * VG * 4) + uint32_t(col) * 16u;
-  const uint32_t ulane = uint32_t(half) * uint32_t(2 * UG * 4) + uint32_t(col) * 16u;
+  using Vec = std::conditional_t<FEW, float2, f32x4>;             // channels of one load
+  constexpr int HG = FEW ? 1 : 2;                                 // loads per lane half and row
+  const uint32_t hoff = FEW ? 8u : uint32_t(2 * VG * 4);
+  const uint32_t vlane = uint32_t(half) * hoff + uint32_t(col) * 16u;
+  const uint32_t ulane = uint32_t(half) * (FEW ? 8u : uint32_t(2 * UG * 4)) + uint32_t(col) * 16u;
   const float* const vblk = V + int64_t(tb) * g.vblock + wave * E * VX;
   const float* const ublk = U + int64_t(kb) * (KB * 4) + wave * E * g.uplane;
 
-  f32x4 ra[4], rb[2];                             // [32-tile half][group of the lane's half]
+  Vec ra[2 * HG], rb[HG];                         // [32-tile half][load of the lane's half]
   auto load = [&](int st, int e) {
     const char* us = reinterpret_cast<const char*>(ublk + e * g.uplane + int64_t(st) * 4 * UG);
     const char* vs = reinterpret_cast<const char*>(vblk + e * VX + int64_t(st) * 4 * VG);
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) rb[jj] = *reinterpret_cast<const f32x4*>(us + jj * UG * 4 + ulane);
+    for (int jj = 0; jj < HG; ++jj) rb[jj] = *reinterpret_cast<const Vec*>(us + jj * UG * 4 + ulane);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-        ra[2 * i + jj] = *reinterpret_cast<const f32x4*>(vs + jj * VG * 4 + vlane + i * 512);
+      for (int jj = 0; jj < HG; ++jj)
+        ra[HG * i + jj] = *reinterpret_cast<const Vec*>(vs + jj * VG * 4 + vlane + i * 512);
   };
 
   f32x16 acc[E][2];
@@ -112,23 +157,35 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
     const int nx = st + 1 < s1 ? st + 1 : st;
     static_for<E>([&](auto I) {
       constexpr int e = decltype(I)::value;
-      const Split8 b = split8(rb[0], rb[1]);
-      const Split8 a0 = split8(ra[0], ra[1]), a1 = split8(ra[2], ra[3]);
-      load(e + 1 < E ? st : nx, (e + 1) % E);
-      // the small terms first
       f32x16 c0 = acc[e][0], c1 = acc[e][1];
-      c0 = mfma_bf16(a0.l, b.h, c0);
-      c1 = mfma_bf16(a1.l, b.h, c1);
-      c0 = mfma_bf16(a0.h, b.l, c0);
-      c1 = mfma_bf16(a1.h, b.l, c1);
-      c0 = mfma_bf16(a0.m, b.m, c0);
-      c1 = mfma_bf16(a1.m, b.m, c1);
-      c0 = mfma_bf16(a0.m, b.h, c0);
-      c1 = mfma_bf16(a1.m, b.h, c1);
-      c0 = mfma_bf16(a0.h, b.m, c0);
-      c1 = mfma_bf16(a1.h, b.m, c1);
-      acc[e][0] = mfma_bf16(a0.h, b.h, c0);
-      acc[e][1] = mfma_bf16(a1.h, b.h, c1);
+      if constexpr (FEW) {
+        // k-step j: channel j in the lower lanes, 2 + j in the upper ones
+        const float2 b = rb[0], a0 = ra[0], a1 = ra[1];
+        load(e + 1 < E ? st : nx, (e + 1) % E);
+        c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, b.x, c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, b.x, c1, 0, 0, 0);
+        c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, b.y, c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, b.y, c1, 0, 0, 0);
+        acc[e][0] = c0;
+        acc[e][1] = c1;
+      } else {
+        const Split8 b = split8(rb[0], rb[1]);
+        const Split8 a0 = split8(ra[0], ra[1]), a1 = split8(ra[2], ra[3]);
+        load(e + 1 < E ? st : nx, (e + 1) % E);
+        // the small terms first
+        c0 = mfma_bf16(a0.l, b.h, c0);
+        c1 = mfma_bf16(a1.l, b.h, c1);
+        c0 = mfma_bf16(a0.h, b.l, c0);
+        c1 = mfma_bf16(a1.h, b.l, c1);
+        c0 = mfma_bf16(a0.m, b.m, c0);
+        c1 = mfma_bf16(a1.m, b.m, c1);
+        c0 = mfma_bf16(a0.m, b.h, c0);
+        c1 = mfma_bf16(a1.m, b.h, c1);
+        c0 = mfma_bf16(a0.h, b.m, c0);
+        c1 = mfma_bf16(a1.h, b.m, c1);
+        acc[e][0] = mfma_bf16(a0.h, b.h, c0);
+        acc[e][1] = mfma_bf16(a1.h, b.h, c1);
+      }
     });
   }
 
@@ -161,7 +218,17 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
         m[1][x] = v.y;
       }
 #pragma unroll
-      for (int p = 0; p < 2; ++p) transform_nd<N, G::A, MM>(m[p], out[p], AT);
+      for (int p = 0; p < 2; ++p) {
+        if constexpr (FEW) {
+          float t[MM * G::A];
+#pragma unroll
+          for (int c = 0; c < G::A; ++c) at_pairs<MM, R>(m[p] + c, G::A, t + c, G::A);
+#pragma unroll
+          for (int o = 0; o < MM; ++o) at_pairs<MM, R>(t + o * G::A, 1, out[p] + o * MM, 1);
+        } else {
+          transform_nd<N, G::A, MM>(m[p], out[p], AT);
+        }
+      }
     }
     if (tail) {
       // partial outputs of this unit: part[pslot][o][t][k], lanes over k

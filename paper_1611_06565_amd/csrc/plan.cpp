@@ -191,6 +191,7 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
 // to 7 stages 25 to 27 there, 27 to 33 here.
 void split4_geometry(wino_plan_s& p) {
   p.split4_parts = 0;
+  p.split4_few = p.C <= 4;
   uint32_t grid = 0;                                // the product's grid at 768 threads
   if (p.kind != 1 || !p.const_mats || !grid_ok(p.grid_gemm, 768, &grid)) return;
   const int nstage = p.C_pad / 16;
@@ -545,7 +546,7 @@ wino_status wino_plan_describe(const wino_plan_t* p, wino_plan_desc* d) {
   d->default_points = p->const_mats ? 1 : 0;
   d->fused = p->fused ? 1 : 0;
   for (int i = 0; i < 3; ++i) { d->tile[i] = p->mv[i]; d->alpha_axis[i] = p->av[i]; }
-  d->gemm_split = p->split4_parts > 0 ? 1 : 0;
+  d->gemm_split = p->split4_parts > 0 ? (p->split4_few ? 2 : 1) : 0;
   d->forward_split = p->fwd_split ? 1 : 0;
   d->forward_parts = p->fwd_split ? p->fwd_parts : (p->fused ? 1 : parts);
   d->wgrad_split = p->wg_fused ? 1 : 0;

@@ -44,6 +44,7 @@ struct wino_plan_s {
   // product runs on k_gemm_acc4 instead) and of k_fwd_split (F(2^3) with
   // fwd_split; 0 otherwise)
   int32_t split4_parts, fwd_parts;
+  bool split4_few;        // k_gemm_split4 multiplies in fp32 (at most four channels)
   int64_t v_floats;       // V in the workspace (rounded up to 256 bytes)
   int64_t part_floats;    // partial outputs after V when nparts > 1
   uint32_t flags;
