@@ -78,8 +78,8 @@ __device__ __forceinline__ void at_pairs(const float* v, int vs, float* out, int
 // against float64 (2-norm, 2 x C x 48 x 64, K = 64) the split products show
 // 1.18, 1.12, 1.07 and 1.04 times k_gemm_acc4's error for 1 to 4 channels, 1.00
 // for 5, 0.97 for 6 and 0.77 for 16; FEW, with at_pairs, 0.98 to 1.00.  FEW also
-// has no splits to make: the forward of 32 x 3 x 224 x 224, K = 64, 248 -> 229
-// us, k_gemm_acc4's 300.
+// has no splits to make: the forward of 32 x 3 x 224 x 224, K = 64, 247 -> 214
+// us (k_gemm_acc4 297).
 //
 // What bounds it: the sum of its parts, which hardly overlap (on 64 x 256 x
 // 56 x 56, K = 256, 535-575 us: matrix work 200 at the clock it falls to, the
@@ -88,11 +88,15 @@ __device__ __forceinline__ void at_pairs(const float* v, int vs, float* out, int
 // splits, but its 36 elements do not fit the registers.  Against the fp32
 // passes of k_gemm_acc4 (us, there / here): that layer 581 / 536;
 // 64 x 512 x 28 x 28, K = 128, 205 / 133; 16 x 16 x 112 x 112, K = 64, 43 / 31;
-// 1 x 3 x 224 x 224, K = 64, 39 / 16.  V is loaded temporally: the kernel
-// blocks of a tile block re-read it (570 -> 531 us against non-temporal loads;
+// 1 x 3 x 224 x 224, K = 64, 39 / 16.  V is loaded temporally while
+// several kernel blocks re-read it (570 -> 531 us against non-temporal loads;
 // the next input transform then finds less of x in the memory-side cache and
-// gives the 40 us back where x is the same tensor each time).
-template <int N, int MM, int R, bool FEW>
+// gives the 40 us back where x is the same tensor each time), and
+// non-temporally with ONE kernel block, where a V past that cache's 256 MB only
+// displaces x and itself.  The whole forward with K = 32 (us, k_gemm_acc4 /
+// temporal / non-temporal): 64 channels, 32768 tiles 155 / 187 / 148; 160
+// channels, 12288 tiles 147 / 164 / 126; 256 channels, 8320 tiles 180 / 185 / 151.
+template <int N, int MM, int R, bool FEW, bool ONE>
 __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict__ V, const float* __restrict__ U,
                                                         float* __restrict__ y, AccArgs g) {
   using G = Split4Geom<N, MM, R>;
@@ -140,8 +144,11 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int jj = 0; jj < HG; ++jj)
-        ra[HG * i + jj] = *reinterpret_cast<const Vec*>(vs + jj * VG * 4 + vlane + i * 512);
+      for (int jj = 0; jj < HG; ++jj) {
+        const char* at = vs + jj * VG * 4 + vlane + i * 512;
+        if constexpr (ONE) ra[HG * i + jj] = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(at));
+        else ra[HG * i + jj] = *reinterpret_cast<const Vec*>(at);
+      }
   };
 
   f32x16 acc[E][2];

@@ -226,7 +226,9 @@ struct Launch {
       acc_args(p, a, G::TB, bias, part);
       if (CONST && p.split4_parts > 0) {
         a.nparts = p.split4_parts;
-        const auto kernel = p.split4_few ? k_gemm_split4<N, MM, R, true> : k_gemm_split4<N, MM, R, false>;
+        const auto kernel = p.split4_few          ? k_gemm_split4<N, MM, R, true, false>
+                            : p.gemm_nkb == 1 ? k_gemm_split4<N, MM, R, false, true>
+                                              : k_gemm_split4<N, MM, R, false, false>;
         hipLaunchKernelGGL(kernel, dim3(p.grid_gemm), dim3(Split4Geom<N, MM, R>::NT), 0, s, V, U, y, a);
       } else {
         hipLaunchKernelGGL((k_gemm_acc4<N, MM, R, CONST>), dim3(p.grid_gemm), dim3(G::NT), 0, s, V, U, y, a, p.fm);
