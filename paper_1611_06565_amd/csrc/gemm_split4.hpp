@@ -70,7 +70,8 @@ __device__ __forceinline__ void at_pairs(const float* v, int vs, float* out, int
 // step for both operands.  No barrier until the channels are done.  Then the
 // products of 32 tiles at a time meet in LDS (144 KB), a thread applies A^T to
 // two (tile, kernel) pairs, and the outputs go through LDS once more so that
-// neighbouring lanes store neighbouring tiles' rows, 16 bytes each.
+// neighbouring lanes store neighbouring tiles' rows, 16 bytes each, or (rows of
+// no whole 16-byte units) neighbouring outputs.
 //
 // FEW (at most four channels): one channel group, lane half h takes channels
 // 2h and 2h + 1 and multiplies them in fp32 (two k-steps an element).  The
@@ -200,6 +201,7 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
   const bool quad = g.Y[1] % 4 == 0;              // rows of whole 16-byte units
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
+    if (!tail && tb * TB + i * HT >= g.T) break;  // no tile of this half
     if (i == 1) __syncthreads();                  // the first half's stores have read ex
     // exchange: ex[element][slot q][lane][4], slot q of a wave's block = rows
     // 8q + 4 half + 0..3 (tiles) of kernel col
@@ -258,14 +260,60 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
               f32x4{out[p][o0 * MM], out[p][o0 * MM + 1], out[p][o0 * MM + 2], out[p][o0 * MM + 3]};
     }
     __syncthreads();
-    // thread = (tile, then kernel and output row): lanes over tiles
+    if (!quad) {
+      // Rows that are no whole 16-byte units: lanes over the outputs of 16
+      // tiles, so that a store covers a run of a row.  (With a tile's four
+      // outputs stored by its lane, each store wrote a quarter of every line it
+      // touched: the forward of 62 x 17 x 138 x 11, K = 161, took 322 us and of
+      // 20 x 4 x 71 x 17, K = 440, 159; so 79 and 39, the fp32 passes 142 and 72.)
+      float* yt[2];
+      int rows[2];                                // output rows of the tile inside y; 0: nothing to store
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t = tb * TB + i * HT + 16 * h + (lane >> 2);
+        int ti[3] = {0, 0, 0};
+        const int n = split_tile<N>(t < g.T ? t : 0, g.tiles, ti);
+        const int ylast = ti[1] * MM + (lane & 3);
+        yt[h] = y + (int64_t(n) * g.K + kb * KB) * g.ystride_k + int64_t(ti[0] * MM) * g.Y[1] + ylast;
+        rows[h] = t < g.T && ylast < g.Y[1] ? g.Y[0] - ti[0] * MM : 0;
+      }
+      const int n_it = MM * (g.K - kb * KB < KB ? g.K - kb * KB : KB);   // (kernel, output row) pairs
+      constexpr int BATCH = 4;                    // reads of LDS ahead of the stores
+      static_assert(((MM - 1) * KB + (MM * KB + BATCH * G::NW) / MM) * G::LDK + HT * MM <= NXI * HT * KB,
+                    "the reads past the last pair stay inside ex");
+#pragma unroll 1
+      for (int it0 = wave; it0 < n_it; it0 += BATCH * G::NW) {
+        float v[BATCH][2];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {         // past the last pair: other words of ex
+          const int it = it0 + b * G::NW, o0 = it % MM, kl = it / MM;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) v[b][h] = ex[(o0 * KB + kl) * G::LDK + lane + 64 * h];
+        }
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+          const int it = it0 + b * G::NW, o0 = it % MM, kl = it / MM;
+          if (it >= n_it) break;
+          const float bk = g.bias != nullptr ? g.bias[kb * KB + kl] : 0.0f;
+          const int64_t off = int64_t(kl) * g.ystride_k + int64_t(o0) * g.Y[1];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            float u = v[b][h];
+            if (g.bias != nullptr) u += bk;
+            u = activate(u, g.act, g.slope);
+            if (o0 < rows[h]) __builtin_nontemporal_store(u, yt[h] + off);
+          }
+        }
+      }
+      continue;
+    }
+    // thread = (tile, then kernel and output row): lanes over tiles, 16 bytes each
     const int tl = tid % HT;
     const int t = tb * TB + i * HT + tl;
     if (t < g.T) {
       int ti[3] = {0, 0, 0};
       const int n = split_tile<N>(t, g.tiles, ti);
       float* const yt = y + int64_t(n) * g.K * g.ystride_k + int64_t(ti[0] * MM) * g.Y[1] + ti[1] * MM;
-      const int left = g.Y[1] - ti[1] * MM;       // outputs of the row inside y
 #pragma unroll 1
       for (int it = tid / HT; it < MM * KB; it += G::NT / HT) {
         const int o0 = it / KB, kl = it % KB, kg = kb * KB + kl;
@@ -277,14 +325,8 @@ __global__ void __launch_bounds__(768, 3) k_gemm_split4(const float* __restrict_
           if (g.bias != nullptr) v[k] += bk;
           v[k] = activate(v[k], g.act, g.slope);
         }
-        float* yo = yt + int64_t(kg) * g.ystride_k + int64_t(o0) * g.Y[1];
-        if (quad) {
-          __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(yo));
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (k < left) __builtin_nontemporal_store(v[k], yo + k);
-        }
+        __builtin_nontemporal_store(
+            v, reinterpret_cast<f32x4*>(yt + int64_t(kg) * g.ystride_k + int64_t(o0) * g.Y[1]));
       }
     }
   }

@@ -28,11 +28,15 @@ SPECS = [
     layer("few_stages_whole", 24, 32, 32, (30, 31)),              # 24 blocks kept whole
     layer("passes_instead", 16, 96, 48, (32, 29)),                # 32 blocks of 6 stages: the fp32 passes
     layer("no_padding", 2, 64, 64, (30, 27), pad=0),
+    layer("rows_of_2_past_a_unit", 3, 20, 70, (5, 66), relu=True),   # stores over two rows of tiles
+    layer("one_output_in_the_last_tile", 2, 16, 5, (6, 129)),      # few kernels, cropped rows
+    layer("rows_of_one_tile", 40, 24, 36, (7, 3)),                # runs of 3 outputs
 ]
 
 
 # layers whose blocks the fp32 passes spread further (not with WINO_NO_SPLIT)
-PASSES = ("one_output", "rows_of_whole_units", "ragged_rows", "half_a_block", "passes_instead")
+PASSES = ("one_output", "rows_of_whole_units", "ragged_rows", "half_a_block", "passes_instead",
+          "one_output_in_the_last_tile")
 
 
 @pytest.mark.parametrize("split", [True, False], ids=["parts", "whole"])
