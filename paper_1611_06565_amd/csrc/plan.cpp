@@ -179,28 +179,44 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   p.fwd_split = true;
 }
 
-// Parts of a tail block of k_gemm_split4 (at most the planner's), or 0 where
-// k_gemm_acc4 is the better one.  A stage of 16 channels takes a block about
-// 3.4 us, splitting costs a whole partial output per part and the sum's
-// launch (4 us for a few blocks, 13 for a hundred).  So few blocks are split
-// down to single stages, and sixteen or more only where that saves at least
-// six stages: 100 blocks of 4 / 8 / 16 stages take 39 / 45 / 61 us in two
-// parts and 26 / 40 / 67 whole.  k_gemm_acc4's parts are runs of its 18
-// passes, so it spreads a block of few stages over more compute units: one
-// or two blocks of 1 to 6 stages 14 us there, 15 here; 16 to 32 blocks of 5
-// to 7 stages 25 to 27 there, 27 to 33 here.
+// Whether the F(4^2) product runs on k_gemm_split4 or on k_gemm_acc4, and over
+// how many parts of a tail block.  Without a tail (full rounds only, or
+// WINO_NO_SPLIT) and for whole rounds before a tail k_gemm_split4 is the faster
+// one (1.0 to 2 times).  What runs in the tail is a chain a work-group walks
+// alone, and the two kernels cut it differently: k_gemm_acc4 into runs of its
+// 18 passes, each of which walks all the channel stages, k_gemm_split4 into
+// runs of channel stages.  So the fp32 passes spread a few blocks of few stages
+// over more compute units; every part costs its partial output and its share
+// of the sum.  In ns:
+//   passes       ceil(18 / parts) (1540 + 390 stages) + 31 parts x tail blocks
+//   split        1070 + 4360 ceil(stages / parts), + 1700 + 90 parts x tail blocks
+//                with more than one part; 800 for at most four channels; whole,
+//                + 1500 on rows of no whole 16-byte units (the sum of the parts
+//                stores those faster)
+// fitted to whole forwards (V just written) of 1,008 layers of 3 to 512
+// channels, 32 to 512 kernels and 1 to 256 tile blocks, every number of parts
+// timed.  On these the choice takes 0.861 of the passes' time in the geometric
+// mean (the fastest of all 0.853) and at most 1.08 times (rows of whole units); e.g. (us, passes /
+// split whole / best parts) 14 blocks of 2 stages 32 / 27 / 26, of 7 stages
+// 33 / 49 / 33; 50 blocks of 7 stages 45 / 52 / 43; 28 of 4 stages 34 / 39 / 36;
+// 4 of 1 stage 22 / 23.
 void split4_geometry(wino_plan_s& p) {
   p.split4_parts = 0;
   p.split4_few = p.C <= 4;
   uint32_t grid = 0;                                // the product's grid at 768 threads
   if (p.kind != 1 || !p.const_mats || !grid_ok(p.grid_gemm, 768, &grid)) return;
-  const int nstage = p.C_pad / 16;
-  if (p.nparts == 1) { p.split4_parts = 1; return; }
-  if (p.nparts >= 16 && p.ntail < 4 && nstage < 8) return;
-  if (p.nparts >= 8 && p.ntail >= 16 && nstage >= 5 && nstage < 8) return;
-  if (p.ntail < 16) { p.split4_parts = p.nparts < nstage ? p.nparts : nstage; return; }
-  const int np = p.nparts < nstage / 2 ? p.nparts : nstage / 2;
-  p.split4_parts = np < 2 || nstage - nstage / np < 6 ? 1 : np;
+  p.split4_parts = 1;
+  if (p.nparts == 1) return;
+  const int64_t stages = p.C_pad / 16, most = p.nparts < stages ? p.nparts : stages;
+  int64_t whole = 0;
+  for (int x = 0; x < 8; ++x) whole += p.acc_xn[x] - p.acc_xs[x];
+  int64_t best = (p.split4_few ? 800 : 1070 + 4360 * stages) + (p.Y[1] % 4 != 0 ? 1500 : 0);
+  for (int64_t np = 2; np <= most; ++np) {
+    const int64_t t = 1070 + 4360 * cdiv(stages, np) + 1700 + 90 * np * p.ntail;
+    if (t < best) { best = t; p.split4_parts = int32_t(np); }
+  }
+  const int64_t passes = cdiv(p.nxi / 2, p.nparts) * (1540 + 390 * stages) + 31 * p.nparts * p.ntail;
+  if (whole == 0 && passes <= best) p.split4_parts = 0;
 }
 
 // Weight-gradient geometry (F(r, m) on the forward's points, V reused): the

@@ -24,7 +24,9 @@ SPECS = [
     layer("half_a_block", 1, 32, 40, (16, 32)),                   # 32 tiles: the block's second half is padding
     layer("past_a_block", 3, 48, 96, (20, 18)),                   # three stages, tiles past one block
     layer("many_parts", 1, 272, 32, (12, 12)),                    # 17 stages in up to 16 uneven parts
-    layer("parts_of_stages", 16, 128, 64, (32, 32)),              # 16 tail blocks of 8 stages in parts
+    layer("parts_of_stages", 16, 128, 64, (32, 32)),              # 32 tail blocks of 8 stages
+    layer("uneven_parts", 24, 200, 64, (32, 32)),                 # 48 blocks of 13 stages in 4 parts
+    layer("tail_after_rounds", 42, 130, 128, (56, 56)),           # full rounds, then 4 blocks in parts
     layer("few_stages_whole", 24, 32, 32, (30, 31)),              # 24 blocks kept whole
     layer("passes_instead", 16, 96, 48, (32, 29)),                # 32 blocks of 6 stages: the fp32 passes
     layer("no_padding", 2, 64, 64, (30, 27), pad=0),
@@ -34,9 +36,9 @@ SPECS = [
 ]
 
 
-# layers whose blocks the fp32 passes spread further (not with WINO_NO_SPLIT)
-PASSES = ("one_output", "rows_of_whole_units", "ragged_rows", "half_a_block", "passes_instead",
-          "one_output_in_the_last_tile")
+# layers whose few blocks the fp32 passes spread further (not with WINO_NO_SPLIT)
+PASSES = ("rows_of_whole_units", "ragged_rows", "half_a_block", "past_a_block", "parts_of_stages", "passes_instead",
+          "no_padding", "rows_of_2_past_a_unit", "one_output_in_the_last_tile", "rows_of_one_tile")
 
 
 @pytest.mark.parametrize("split", [True, False], ids=["parts", "whole"])
