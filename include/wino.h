@@ -285,9 +285,11 @@ wino_status wino_gemm_inverse(const wino_plan_t* plan, void* workspace, size_t w
 
 /* The whole forward (eq. 4 with eq. 5) on one stream, with
  * wino_forward_workspace_bytes(plan) bytes of workspace (workspace may be
- * NULL when that is 0).  F(2^3, 3^3) plans with the default points, whole
- * groups of 16 channels, pad 1 and a multiple of 4 along the last axis, and
- * at least two to three tiles per kernel (x at most 512 MiB) form the transformed input inside the product as well; their
+ * NULL when that is 0).  Plans with desc.forward_split = 1 form the
+ * transformed input inside the product as well: F(2^3, 3^3) with the default
+ * points, C a multiple of 16 and at least 8 ceil(K / 64), pad 1 and a
+ * multiple of 4 along the last axis, x at most 512 MiB, and enough tiles for
+ * the kernels (T_pad >= 3 K_pad, or T_pad >= 2 K_pad and T_pad >= 512).  Their
  * workspace holds the kernels split for it instead of V, so the
  * wino_transform_input + wino_gemm_inverse pair may differ from wino_forward
  * in the last bits.  Other two-stage plans run wino_transform_input and then

@@ -162,6 +162,13 @@ bool acc_geometry(wino_plan_s& p, const SizeTraits& t, bool split, int cus) {
 // tiles a kernel the splitting of U outweighs V's traffic: 256 channels to 256
 // kernels with 448 tiles (1.75 a kernel) 59 / 58, with 576 82 / 90; 64 to 128
 // with 320 tiles 31.3 / 30.8, with 448 31 / 32.
+// V is formed again for every block of 64 kernels, a cost per tile and block
+// that few channels' products do not hide, while the V traffic saved grows with
+// the channels and not with the kernels: at 4 x 16 x 28 x 56 16 channels to 128 /
+// 256 / 512 kernels 83 / 163 / 269 against 85 / 152 / 232, 32 to 256 / 512 213 /
+// 345 against 218 / 325, 48 to 384 192 against 190 (1 x 16 x 56 x 56), 64 to 512
+// 1.02 times the faster.  So one stage while there are at least eight channels
+// for each block of kernels (at the line: 0.97 to 1.02).
 void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   p.fwd_split = false;
   p.fwd_parts = 0;
@@ -172,6 +179,7 @@ void fwd_split_geometry(wino_plan_s& p, int64_t uf) {
   if (!mul3_ok(p.X[0], p.X[1], p.X[2], &xs) || !mul3_ok(xs, int64_t(p.C), p.batch, &xn) || xn > lim) return;
   const int64_t tk = p.T_pad / p.K_pad;             // (the split kernels take 3/2 of U)
   if (tk < 2 || (tk < 3 && p.T_pad < 512)) return;
+  if (8 * int64_t(p.gemm_nkb) > p.C) return;
   uint32_t grid = 0;                                // the product's grid at 512 threads
   if (!grid_ok(p.grid_gemm, 512, &grid) || !grid_ok(cdiv(uf / 8, 256), 256, &p.grid_split_u)) return;
   const int64_t units = int64_t(p.nxi / 8) * (p.C_pad / 16);   // (pass of eight elements, channel stage) steps

@@ -183,6 +183,13 @@ int main() {
               d.forward_split == 0 && d.wgrad_split == 0 && d.wgrad_ranges >= 1 && d.forward_parts == d.gemm_parts,
           "F(2^3), rows not a multiple of 4: the fp32 products");
     wino_destroy(p);
+    const int32_t ck[6][3] = {{16, 128, 1}, {16, 129, 0}, {32, 256, 1}, {32, 257, 0}, {64, 512, 1}, {64, 513, 0}};
+    for (const auto& c : ck) {
+      p = nullptr;
+      if (plan_status(3, 2, 3, c[0], c[1], d3, 1, &p) != WINO_OK || wino_plan_describe(p, &d) != WINO_OK) std::abort();
+      CHECK(d.forward_split == c[2], "F(2^3): eight channels for each block of kernels");
+      wino_destroy(p);
+    }
     wino_opts o{};
     o.pad[0] = o.pad[1] = o.pad[2] = 1;
     o.flags = WINO_NO_FUSE;

@@ -21,7 +21,8 @@ INSIDE = [
     layer("three_tiles_a_kernel", 1, 16, 1, (2, 16, 40)),          # 160 tiles (192 padded) for 64 kernels, one stage
     layer("odd_first_axes", 2, 32, 70, (7, 11, 36), relu=True),   # cropped tiles, ragged kernel block
     layer("ragged_tile_block", 3, 48, 64, (5, 7, 12), leaky=0.2),  # T past a whole block, three stages
-    layer("rows_of_66_tiles", 1, 16, 130, (8, 6, 132)),           # rows longer than a wave's 32 tiles
+    layer("rows_of_66_tiles", 1, 32, 130, (8, 6, 132)),           # rows longer than a wave's 32 tiles
+    layer("two_blocks_of_kernels", 1, 16, 128, (8, 6, 132)),      # the last with 16 channels
     layer("rows_of_32_tiles", 2, 64, 128, (4, 8, 64)),            # rows end where the wave's tiles do
     layer("rows_of_2_tiles", 5, 16, 3, (9, 13, 4)),               # every pair of tiles is a row
     layer("whole_blocks", 8, 32, 64, (16, 56, 56)),               # full rounds and a split tail
@@ -30,6 +31,7 @@ OUTSIDE = [
     layer("row_not_of_4", 2, 32, 64, (7, 11, 34)),
     layer("channels_not_of_16", 1, 24, 64, (8, 12, 32)),
     layer("no_padding", 2, 32, 64, (10, 12, 36), pad=0),
+    layer("three_blocks_of_kernels", 1, 16, 130, (8, 6, 132)),    # too few channels for them
     layer("few_tiles_a_kernel", 1, 16, 400, (2, 4, 8)),
     layer("one_pair_of_tiles", 1, 16, 1, (1, 1, 4)),
 ]
