@@ -277,13 +277,22 @@ void wgrad_geometry(wino_plan_s& p, const SizeTraits& t, const Rat* pts, const R
 // leading axis of one position inside its padding, where the outer taps sum
 // nothing and their exact zeros show what is left of products that cancel
 // (normalised error 0.8e-4 to 1.3e-4 against 0.5e-4 to 0.8e-4 on 1 x 28 x 28
-// and 28 x 1 x 28, with the library's bar at 1e-4).  The ranges fill
-// the chip with one work-group a compute unit (each costs a partial M, kept
-// where V and D would be).  Measured against the form with V and D in memory
-// (us, here / there): 8 x 64 x 16 x 56 x 56 to 128 kernels 567 / 1069,
-// 8 x 3 x 16 x 56 x 56 to 64 289 / 454, 4 x 256 x 8 x 28 x 28 to 256 298 / 399,
-// 4 x 512 x 2 x 8 x 8 to 512 210 / 224, one channel and kernel 20 / 25: no size
-// of these was slower.
+// and 28 x 1 x 28, with the library's bar at 1e-4).  One
+// work-group runs a compute unit, and its 16-tile steps are a chain, so blocks x
+// ranges should come to whole rounds of the compute units; each range costs a
+// partial M (kept where V and D would be).  The count of ranges, and whether the
+// form with V and D in memory is the faster one (its product has many more,
+// shorter work-groups), follow from what differs between the two, in us:
+//   here    rounds x steps a range x 4.02 (2.52 for at most 64 kernels)
+//           + 0.155 a MB of partial M
+//   there   8.7 + 1.855 x tile blocks a range x rounds of 512 work-groups
+//           + 0.195 a MB of V and D + 0.169 a MB of partial M
+// fitted to 364 layers of 1 to 3136 steps, 1 to 768 channels and kernels, every
+// count of ranges timed: 0.862 of the other form's time in the mean (the fastest
+// of all 0.856), at most 1.06 times.  E.g. (us, one range a compute unit at most /
+// now / V and D in memory) 4 x 8 x 28 x 28: 384 to 384 1027 / 779 / 783, 448 to
+// 320 1037 / 777 / 777; 2 x 4 x 28 x 28, 512 to 640 673 / 594 / 582; 4 x 2 x 8 x 8,
+// 96 to 96 46 / 38 / 38.  8 x 64 x 16 x 56 x 56 to 128 kernels takes 567 against 1069.
 void wgrad_split_geometry(wino_plan_s& p, int cus) {
   p.wg_fused = false;
   p.wg_fused_ranges = 0;
@@ -298,14 +307,22 @@ void wgrad_split_geometry(wino_plan_s& p, int cus) {
   if (!mul3_ok(p.Y[0], p.Y[1], p.Y[2], &yn) || !mul3_ok(yn, int64_t(p.K), p.batch, &yn) || yn > lim) return;
   const int64_t nkb = cdiv(p.wg_kpad4, 64), ncb = cdiv(p.C_pad, 64);
   const int64_t blocks = 8 * (p.K > 64 ? cdiv(nkb, 2) : 1) * ncb, steps = cdiv(p.T, 16);
-  int64_t ns = (cus > 0 ? cus : 256) / blocks;
+  const int64_t cu = cus > 0 ? cus : 256;
   const int64_t plane = 64 * nkb * 64 * ncb * 64;   // floats of one range's M
   const int64_t room = (p.v_floats + p.wg_d_floats + p.wg_part_floats) / plane;
-  ns = ns < steps ? ns : steps;
-  ns = ns < room ? ns : room;
+  const double mb = 4e-6 * double(plane);
+  int64_t ns = 0;
+  double best = 0.0;
+  for (int64_t n = 1; n <= steps && n <= room && (n == 1 || blocks * n <= 8 * cu); ++n) {
+    const double t = double(cdiv(blocks * n, cu) * cdiv(steps, n)) * (p.K > 64 ? 4.02 : 2.52) + 0.155 * mb * double(n);
+    if (ns == 0 || t < best) { best = t; ns = n; }
+  }
+  const double groups = double(64 * nkb * ncb * p.wg_nsplit);
+  const double there = 8.7 + 1.855 * double(cdiv(cdiv(p.T, 64), p.wg_nsplit)) * (groups > 512 ? groups / 512 : 1.0) +
+                       0.195 * 4e-6 * 64 * 64 * double(cdiv(p.T, 64)) * double(p.C_pad + p.wg_kpad4) +
+                       0.169 * mb * double(p.wg_nsplit);
   uint32_t grid = 0;
-  ns = ns < 1 ? 1 : ns;
-  if (room < 1 || !grid_ok(blocks * ns, 512, &grid)) return;
+  if (ns == 0 || there <= best || !grid_ok(blocks * ns, 512, &grid)) return;
   p.wg_fused_ranges = int32_t(ns);
   p.wg_fused = true;
 }

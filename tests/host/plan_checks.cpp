@@ -213,7 +213,7 @@ int main() {
           "F(4^2), caller's points: the fp32 passes");
     wino_destroy(p);
     const int64_t thin[4] = {2, 1, 16, 16}, flat[4] = {2, 16, 1, 16}, few[4] = {1, 2, 2, 12}, some[4] = {1, 2, 2, 16},
-                  wide[4] = {1, 1, 16, 16};
+                  wide[4] = {64, 1, 16, 16};
     const int64_t* ds[4] = {thin, flat, few, some};
     for (int i = 0; i < 4; ++i) {
       p = nullptr;
@@ -221,6 +221,28 @@ int main() {
       CHECK(d.wgrad_split == (i == 3), "weight gradient of thin and short layers on the fp32 products");
       wino_destroy(p);
     }
+    // whole rounds of the compute units: 144 blocks of work-groups (384 channels,
+    // 384 kernels) run in several ranges, not as 144 of 256
+    const int64_t d8[4] = {4, 8, 28, 28}, deep[4] = {8, 16, 28, 28};
+    p = nullptr;
+    CHECK(plan_status(3, 2, 3, 384, 384, d8, 1, &p) == WINO_OK && wino_plan_describe(p, &d) == WINO_OK &&
+              d.wgrad_split == 1 && (144 * d.wgrad_ranges) % 256 * 8 >= 7 * 256,
+          "weight gradient, 144 blocks: nearly whole rounds");
+    wino_destroy(p);
+    for (int C = 64; C <= 640; C += 64)
+      for (int K = 64; K <= 640; K += 64) {
+        p = nullptr;
+        if (plan_status(3, 2, 3, C, K, deep, 1, &p) != WINO_OK || wino_plan_describe(p, &d) != WINO_OK) std::abort();
+        const int blocks = 8 * (K > 64 ? (K + 127) / 128 : 1) * (C / 64), groups = blocks * d.wgrad_ranges;
+        const size_t m = size_t(4) * 64 * ((K + 63) / 64 * 64) * C;
+        if (d.wgrad_split == 1 && (groups * 10 < (groups + 255) / 256 * 256 * 7 ||
+                                   m * d.wgrad_ranges > wino_weight_gradient_workspace_bytes(p))) {
+          std::fprintf(stderr, "FAIL: C = %d, K = %d: %d work-groups\n", C, K, groups);
+          return 1;
+        }
+        wino_destroy(p);
+      }
+    std::printf("ok: weight gradient's work-groups fill at least 0.7 of their rounds\n");
     o = wino_opts{};
     o.pad[0] = 2; o.pad[1] = o.pad[2] = 1;
     p = nullptr;

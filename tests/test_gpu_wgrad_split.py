@@ -22,8 +22,10 @@ LAYERS = [
     ("ragged_blocks", 1, 130, 200, (4, 6, 8)),          # three channel blocks, 128 + 72 kernels
     ("uneven_ranges", 3, 20, 96, (9, 17, 20)),
 ]
-# too short a contraction, or a leading axis of one position: the fp32 products
+# too short a contraction, a leading axis of one position, or a chain of steps
+# longer than V and D take: the fp32 products
 FP32 = [
+    ("four_steps_of_two_blocks", 4, 96, 96, (2, 8, 8)),
     ("one_row_of_two_tiles", 1, 1, 1, (1, 1, 4)),
     ("two_tiles", 1, 1, 1, (2, 2, 4)),
     ("six_tiles", 1, 3, 2, (2, 2, 12)),
