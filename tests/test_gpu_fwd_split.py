@@ -25,7 +25,8 @@ INSIDE = [
     layer("two_blocks_of_kernels", 1, 16, 128, (8, 6, 132)),      # the last with 16 channels
     layer("rows_of_32_tiles", 2, 64, 128, (4, 8, 64)),            # rows end where the wave's tiles do
     layer("rows_of_2_tiles", 5, 16, 3, (9, 13, 4)),               # every pair of tiles is a row
-    layer("whole_blocks", 8, 32, 64, (16, 56, 56)),               # full rounds and a split tail
+    layer("whole_blocks", 8, 32, 64, (16, 56, 56)),               # full rounds, nothing in parts
+    layer("tail_after_rounds", 15, 16, 64, (8, 48, 48)),          # full rounds, then blocks in parts
 ]
 OUTSIDE = [
     layer("row_not_of_4", 2, 32, 64, (7, 11, 34)),
@@ -81,4 +82,57 @@ def test_error_no_larger_than_two_stages():
             y = plan.forward(torch.from_numpy(x).cuda(), plan.transform_filter(torch.from_numpy(w).cuda()))
             err.append(np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref))
         print(C, dist, err)
-        assert err[0] <= 1.05 * err[1], (C, dist, err)
+        assert err[0] <= err[1], (C, dist, err)
+
+
+def _forward(dims, C, K, pad, x, w):
+    import torch
+
+    from paper_1611_06565_amd.wino import Plan
+    plan = Plan(3, 2, 3, C, K, dims, pad=pad, split=False)
+    assert plan.desc["forward_split"] == 1
+    y = plan.forward(torch.from_numpy(np.ascontiguousarray(x)).cuda(), plan.transform_filter(torch.from_numpy(w).cuda()))
+    return y.cpu().numpy()
+
+
+def test_bitwise_invariants():
+    """What needs no oracle value: a shift by one tile along an unpadded axis, a
+    sample alone, and a doubled input give the same bits (whole blocks)."""
+    C, K = 32, 70
+    pad = [0, 0, 1]
+    spec = layer("inv", 2, C, K, (10, 13, 36))
+    x, w = draw_layer(spec, seed=43)
+    y = _forward([2, 10, 13, 36], C, K, pad, x, w)
+    assert np.array_equal(_forward([2, 8, 13, 36], C, K, pad, x[:, :, 2:], w), y[:, :, 2:])
+    assert np.array_equal(_forward([2, 10, 11, 36], C, K, pad, x[:, :, :, 2:], w), y[:, :, :, 2:])
+    for b in range(2):
+        assert np.array_equal(_forward([1, 10, 13, 36], C, K, pad, x[b:b + 1], w)[0], y[b])
+    assert np.array_equal(_forward([2, 10, 13, 36], C, K, pad, 2 * x, w), 2 * y)
+
+
+def test_integer_inputs_bitwise_exact():
+    """Integers in [-2, 2]: every split, product and sum is exact."""
+    from oracle.direct import direct_blas
+    rng = np.random.default_rng(3)
+    x = rng.integers(-2, 3, size=(2, 32, 7, 12, 36)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(70, 32, 3, 3, 3)).astype(np.float32)
+    ref, _ = direct_blas(x, w, 1)
+    assert np.array_equal(_forward([2, 7, 12, 36], 32, 70, 1, x, w), ref.astype(np.float32))
+
+
+@pytest.mark.parametrize("xs,ws", [(2.0 ** -110, 1.0), (1.0, 2.0 ** -108), (2.0 ** -60, 2.0 ** -60), (2.0 ** 60, 2.0 ** 50)])
+def test_magnitudes(xs, ws):
+    """The three parts of a value hold all its bits while the last is a normal
+    bf16 number (values from about 2^-112 up), and the products' small terms are
+    not flushed: the relative error is that of values around 1 (2-norms over
+    131,072 outputs: 5% leaves them their spread)."""
+    from oracle.direct import direct_blas
+    rng = np.random.default_rng(2)
+    x = rng.standard_normal((4, 32, 8, 8, 16), dtype=np.float32)
+    w = (0.05 * rng.standard_normal((32, 32, 3, 3, 3))).astype(np.float32)
+    err = []
+    for a, b in ((1.0, 1.0), (xs, ws)):
+        sx, sw = x * np.float32(a), w * np.float32(b)
+        ref, _ = direct_blas(sx, sw, 1)
+        err.append(np.linalg.norm(_forward([4, 8, 8, 16], 32, 32, 1, sx, sw) - ref) / np.linalg.norm(ref))
+    assert err[1] <= 1.05 * err[0], err

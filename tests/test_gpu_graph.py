@@ -25,6 +25,16 @@ CASES = [
                x_dist="normal", w_dist="he"), {"split": True, "fuse": True}),
     (LayerSpec("g_f4x3_3d_two_stage", N=3, m=4, r=3, batch=1, C=20, K=24, X=(13, 11, 17), pad=1,
                x_dist="normal", w_dist="he"), {"split": True, "fuse": False}),
+    # F(2^3) in one kernel (k_split_u, k_fwd_split, k_part_reduce), and whole
+    (LayerSpec("g_f2x3_one_kernel", N=3, m=2, r=3, batch=4, C=32, K=48, X=(7, 12, 16), pad=1,
+               x_dist="normal", w_dist="he"), {"split": True}),
+    (LayerSpec("g_f2x3_one_kernel_nosplit", N=3, m=2, r=3, batch=4, C=32, K=48, X=(7, 12, 16), pad=1,
+               x_dist="normal", w_dist="he", relu=True), {"split": False}),
+    # F(4^2) on the split product: parts of channel stages, whole, and fp32 for few channels
+    (LayerSpec("g_f4x3_2d_split_parts", N=2, m=4, r=3, batch=1, C=272, K=32, X=(12, 12), pad=1,
+               x_dist="normal", w_dist="he"), {"split": True}),
+    (LayerSpec("g_f4x3_2d_few_channels", N=2, m=4, r=3, batch=2, C=3, K=70, X=(33, 35), pad=1,
+               x_dist="normal", w_dist="he"), {"split": False}),
     # per-axis tiles F(2,3) x F(4,3)^2
     (LayerSpec("g_aniso_244", N=3, m=2, r=3, batch=2, C=12, K=20, X=(10, 15, 13), pad=1,
                x_dist="normal", w_dist="he", tile=(2, 4, 4)), {"split": True}),
@@ -51,6 +61,9 @@ def test_forward_graph_replay(spec, kw):
                 relu=spec.relu, tile=spec.tile, **kw)
     if "fuse" in kw:
         assert plan.desc["fused"] == (1 if kw["fuse"] else 0)
+    assert plan.desc["forward_split"] == ("one_kernel" in spec.name)
+    if "split_parts" in spec.name or "few_channels" in spec.name:
+        assert plan.desc["gemm_split"] == (1 if spec.C > 4 else 2) and (plan.desc["gemm_parts"] > 1) == kw["split"]
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     U = plan.transform_filter(wd)
     ws = plan.new_workspace()
@@ -71,14 +84,15 @@ def test_forward_graph_replay(spec, kw):
     _replay_check(torch, g, y, eager, scratch)
 
 
-def test_gradients_graph_replay():
+@pytest.mark.parametrize("spec", [CASES[0][0], CASES[5][0]], ids=["two_stage", "split_products"])
+def test_gradients_graph_replay(spec):
     torch = require_gpu()
     from paper_1611_06565_amd.wino import Plan
-    log("[gpu] graph gradients")
-    spec = CASES[0][0]
+    log(f"[gpu] graph gradients {spec.name}")
     x, w = draw_layer(spec, seed=22)
     plan = Plan(spec.N, spec.m, spec.r, spec.C, spec.K, [spec.batch] + list(spec.X), pad=spec.pad)
     adj = plan.adjoint()
+    assert adj.desc["forward_split"] == plan.desc["wgrad_split"] == ("one_kernel" in spec.name)
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     dyd = torch.from_numpy(np.random.default_rng(3).standard_normal(plan.output_shape, dtype=np.float32)).cuda()
     Ua = adj.transform_filter_adjoint(wd)
@@ -109,8 +123,10 @@ def test_gradients_graph_replay():
 
 @pytest.mark.parametrize("case,fuse,window,split",
                          [(3, True, (1, 2, 2), True), (3, False, (2, 2, 2), True),
-                          (0, False, (2, 2, 2), True), (1, False, (2, 2, 2), False)],
-                         ids=["fused_122", "two_stage_222", "f2x3_parts_222", "f2x3_nosplit_222"])
+                          (0, False, (2, 2, 2), True), (1, False, (2, 2, 2), False),
+                          (5, True, (2, 2, 2), True), (6, True, (2, 2, 2), False)],
+                         ids=["fused_122", "two_stage_222", "f2x3_parts_222", "f2x3_nosplit_222",
+                              "f2x3_one_kernel_parts_222", "f2x3_one_kernel_nosplit_222"])
 def test_forward_pool_graph_replay(case, fuse, window, split):
     """wino_forward_pool under capture: the fused F(4^3) forward, the
     two-stage one and the F(2^3) one (split into parts reduced and pooled
@@ -122,12 +138,13 @@ def test_forward_pool_graph_replay(case, fuse, window, split):
     x, w = draw_layer(spec, seed=23)
     plan = Plan(spec.N, spec.m, spec.r, spec.C, spec.K, [spec.batch] + list(spec.X), pad=spec.pad,
                 relu=True, fuse=fuse, split=split)
-    assert plan.desc["fused"] == (1 if fuse else 0)
+    assert plan.desc["fused"] == (1 if fuse and spec.m == 4 else 0)
+    assert plan.desc["forward_split"] == (case in (5, 6))
     if case == 0:
         assert plan.desc["gemm_parts"] > 1, "the split case must split"
     xd, wd = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
     U = plan.transform_filter(wd)
-    ws = plan.new_workspace() if not fuse else None
+    ws = plan.new_workspace() if not plan.desc["fused"] else None
     y = torch.empty(plan.pooled_shape(window), device="cuda")
     plan.forward_pool(xd, U, window, y=y, workspace=ws)
     torch.cuda.synchronize()

@@ -65,6 +65,18 @@ M2 = [
     (LayerSpec("pool_m2_c5_k16_pad0_noact", N=3, m=2, r=3, batch=1, C=5, K=16, X=(9, 10, 11), pad=0,
                x_dist="normal", w_dist="normal"), True),
 ]
+# F(2^3) in one kernel (k_fwd_split<1>): cropped tiles and a ragged block of
+# kernels, in parts and whole, each activation
+ONE_KERNEL = [
+    (LayerSpec("pool_one_kernel_odd_relu", N=3, m=2, r=3, batch=2, C=32, K=70, X=(7, 11, 36), pad=1,
+               x_dist="normal", w_dist="he", relu=True), True),
+    (LayerSpec("pool_one_kernel_odd_relu_unsplit", N=3, m=2, r=3, batch=2, C=32, K=70, X=(7, 11, 36), pad=1,
+               x_dist="normal", w_dist="he", relu=True), False),
+    (LayerSpec("pool_one_kernel_leaky", N=3, m=2, r=3, batch=3, C=48, K=64, X=(5, 7, 12), pad=1,
+               x_dist="normal", w_dist="he", leaky=0.125), True),
+    (LayerSpec("pool_one_kernel_noact_unsplit", N=3, m=2, r=3, batch=5, C=16, K=3, X=(9, 13, 4), pad=1,
+               x_dist="normal", w_dist="normal"), False),
+]
 
 
 def _run(spec, window, seed, bias=True, fuse=True, split=True):
@@ -78,6 +90,7 @@ def _run(spec, window, seed, bias=True, fuse=True, split=True):
     assert plan.desc["fused"] == (1 if fuse and spec.m == 4 and spec.K <= 64 else 0)
     if spec.m == 2:
         assert (plan.desc["gemm_parts"] > 1) == split, plan.desc
+        assert plan.desc["forward_split"] == fuse and (plan.desc["forward_parts"] > 1) == split, plan.desc
     xd = torch.from_numpy(x).cuda()
     U = plan.transform_filter(torch.from_numpy(w).cuda())
     bd = torch.from_numpy(b).cuda() if bias else None
@@ -96,8 +109,9 @@ def _run(spec, window, seed, bias=True, fuse=True, split=True):
 
 @pytest.mark.parametrize("spec,window,fuse,split",
                          [c + (True, True) for c in CASES] + [c + (False, True) for c in TWO_STAGE]
-                         + [(c[0], (2, 2, 2), False, c[1]) for c in M2],
-                         ids=[c[0].name for c in CASES] + [c[0].name for c in TWO_STAGE] + [c[0].name for c in M2])
+                         + [(c[0], (2, 2, 2), False, c[1]) for c in M2]
+                         + [(c[0], (2, 2, 2), True, c[1]) for c in ONE_KERNEL],
+                         ids=[c[0].name for c in CASES + TWO_STAGE + M2 + ONE_KERNEL])
 def test_forward_pool_matches_forward_then_pool_and_oracle(spec, window, fuse, split):
     x, w, b, yp, y2 = _run(spec, window, seed=41, fuse=fuse, split=split)
     assert yp.shape == y2.shape

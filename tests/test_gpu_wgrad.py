@@ -58,6 +58,8 @@ def run_wgrad(N, m, r, batch, C, K, X, pad, x_fn, dy_fn, name, points=None):
     log(f"[gpu] wgrad {name} N={N} m={m} r={r} C={C} K={K} X={X} batch={batch} pad={pad} points={points}")
     plan = Plan(N, m, r, C, K, [batch] + list(X), pad=pad, points=points)
     assert plan.weight_gradient_workspace_bytes > 0
+    if name in ("int", "det1", "det2"):
+        assert plan.desc["wgrad_split"] == (X[2] % 4 == 0)
     x = x_fn(plan.input_shape)
     dy = dy_fn(plan.output_shape)
     dw = plan.weight_gradient(torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda())
@@ -97,24 +99,27 @@ def test_wgrad_caller_points(N, m, points):
     _check(dw, x, dy, 3, 1)
 
 
-def test_wgrad_integer_inputs_bitwise_exact():
+# rows of 7 (the fp32 products) and of 8 and 36 (both transforms inside the product)
+@pytest.mark.parametrize("X", [(5, 9, 7), (5, 9, 8), (6, 13, 36)], ids=str)
+def test_wgrad_integer_inputs_bitwise_exact(X):
     # F(2^3): F(3, 2)'s matrices hold 0, +-1 and +-1/2 only, so small-integer
     # data keeps every intermediate an exact fp32 value
     rng = np.random.default_rng(6)
-    dw, x, dy = run_wgrad(3, 2, 3, 2, 12, 20, (5, 9, 7), 1,
+    dw, x, dy = run_wgrad(3, 2, 3, 2, 12, 20, X, 1,
                           lambda s: rng.integers(-2, 3, size=s).astype(np.float32),
                           lambda s: rng.integers(-2, 3, size=s).astype(np.float32), "int")
     ref, _ = direct_wgrad(x, dy, 3, 1, with_den=False)
     assert np.array_equal(dw, ref.astype(np.float32))
 
 
-def test_wgrad_determinism_bitwise():
+@pytest.mark.parametrize("X", [(6, 13, 15), (6, 13, 16)], ids=str)
+def test_wgrad_determinism_bitwise(X):
     rng = np.random.default_rng(7)
     shp = {}
     x_fn = lambda s: shp.setdefault("x", rng.standard_normal(s).astype(np.float32))   # noqa: E731
     dy_fn = lambda s: shp.setdefault("dy", rng.standard_normal(s).astype(np.float32))  # noqa: E731
-    a, _, _ = run_wgrad(3, 2, 3, 2, 24, 40, (6, 13, 15), 1, x_fn, dy_fn, "det1")
-    b, _, _ = run_wgrad(3, 2, 3, 2, 24, 40, (6, 13, 15), 1, x_fn, dy_fn, "det2")
+    a, _, _ = run_wgrad(3, 2, 3, 2, 24, 40, X, 1, x_fn, dy_fn, "det1")
+    b, _, _ = run_wgrad(3, 2, 3, 2, 24, 40, X, 1, x_fn, dy_fn, "det2")
     assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
 
 
