@@ -33,6 +33,19 @@
  * - Argument and shape errors are reported synchronously with a negative
  *   wino_status and leave every buffer untouched.  Launch failures return
  *   WINO_EDEVICE.  Nothing aborts or throws across the ABI.
+ * - Arithmetic is fp32.  Where wino_plan_describe says gemm_split = 1,
+ *   forward_split = 1 or wgrad_split = 1, the products run on the bf16 matrix
+ *   cores: each transformed value as the sum of three bf16 numbers (exact from
+ *   about 2^-112 up in magnitude, to 2^-133 absolute below), the six largest of
+ *   the nine partial products (those left out are below 2^-22 of the product,
+ *   about 2^-26 in the mean) and fp32 accumulators.  Plans take these kernels
+ *   only where their error against exact results is not larger than the fp32
+ *   products'.
+ * - Inputs must be finite, and so must the transformed values.  A NaN or an
+ *   infinity reaches outputs of every tile whose window holds it, as a NaN or an
+ *   infinity, and always as a NaN through the split products.  Activations and
+ *   max-pools compare with ">": a ReLU turns a NaN into 0, and a NaN never wins a
+ *   pool (a window of nothing else gives -infinity).
  * - A plan is immutable after wino_plan returns; it may be used from several
  *   host threads and streams at once provided each call gets its own
  *   workspace and output buffers.
@@ -65,9 +78,8 @@ typedef struct wino_plan_s wino_plan_t; /* opaque, immutable after creation */
  *                    (slope = wino_opts.slope, finite) */
 #define WINO_RELU 1u
 #define WINO_LEAKY_RELU 4u
-/* Never split the channel-element passes of a product block over several
- * work-groups (no partials scratch in the workspace; see
- * wino_workspace_bytes). */
+/* Never split a forward product's block over several work-groups (no partials
+ * scratch in the workspace; see wino_workspace_bytes). */
 #define WINO_NO_SPLIT 2u
 /* Keep the forward of an F(4^3, 3^3) layer with at most 64 kernels, or of an
  * F(2^3, 3^3) layer that wino_forward would run in one kernel, in two stages
@@ -335,7 +347,7 @@ wino_status wino_maxpool3d(const int64_t* dims, const int32_t* window, const flo
 
 /* wino_forward_ex followed by wino_maxpool3d, with the pooling inside the
  * product's epilogue, so only the pooled outputs reach memory: F(4^3)
- * plans, fused (wino_plan_info.fused = 1, no workspace) or in two stages
+ * plans, fused (wino_plan_desc.fused = 1, no workspace) or in two stages
  * (the input transform to the workspace, then the product), and F(2^3)
  * plans with window (2, 2, 2) (a window is one tile).  eq. (2)'s f
  * (the plan's activation) is applied before the maximum, as a pooling layer

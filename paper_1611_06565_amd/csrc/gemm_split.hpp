@@ -1,22 +1,32 @@
 // The F(2^3, 3^3) forward in one kernel (k_fwd_split), on the bf16 matrix
 // cores with fp32 operands split into three bf16 numbers each.
 //
-// The split.  a = a1 + a2 + a3: a1 the upper 16 bits of a (truncated: it never
+// The split (of fp32 values into three bf16 and products of their leading
+// terms: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", ARITH
+// 2019).  a = a1 + a2 + a3: a1 the upper 16 bits of a (truncated: it never
 // overflows), a2 the bf16 nearest to a - a1, a3 the bf16 nearest to the rest;
-// the subtractions are exact, and a1 + a2 + a3 misses a by less than
-// 2^-24 |a|.  A product a b is the sum of the six terms a1 b1, a1 b2, a2 b1,
-// a1 b3, a2 b2, a3 b1, each exact in fp32; what is left out (a2 b3, a3 b2,
-// a3 b3) is below 2^-22 |a b|, about 2^-26 in the mean and of random sign.
-// The sums stay in fp32 MFMA accumulators.  One v_mfma_f32_32x32x16_bf16 sums
-// 16 channels with one rounding of the accumulator, and six of them replace
-// eight v_mfma_f32_32x32x2_f32: against float64, products over 64 / 256 / 512
-// channels of normal values show a relative error (2-norm) of 1.1e-7 / 2.4e-7
-// / 3.4e-7 where the fp32 instruction shows 1.4e-7 / 2.9e-7 / 4.1e-7, and the
-// forward of 8 x 64 x 16 x 56 x 56, K = 128, 2.6e-7 against 3.1e-7.
+// the subtractions are exact, and so is the sum (8 + 16 bits, of which a2 takes
+// 8 and its sign leaves 8) while a3 is a normal bf16 number: for |a| from about
+// 2^-112 up.  Below, a3 loses bits, to 2^-133 absolute.  A product a b is the sum of
+// the six terms a1 b1, a1 b2, a2 b1, a1 b3, a2 b2, a3 b1, each exact; what is left
+// out (a2 b3, a3 b2, a3 b3) is below 2^-22 |a b|, about 2^-26 in the mean and of
+// random sign.  Small terms are not flushed: errors are the same with every
+// product near 2^-120.  An infinity's remainder a - a1 is a NaN.
 //
-// Why.  fp32 MFMA gives 157 TFLOP/s (142 in a plain loop), bf16 2.5 PFLOP/s
-// (1.8 in a plain loop on random values, where the clock falls to 1.7 GHz);
-// at six products a term that is 300.
+// The sums stay in fp32 MFMA accumulators.  One v_mfma_f32_32x32x16_bf16 sums
+// 16 channels with fewer roundings of the accumulator than the eight
+// v_mfma_f32_32x32x2_f32 it replaces; six of them, against float64, products over
+// 64 / 256 / 512 channels of normal values: relative error (2-norm) of 1.1e-7 /
+// 2.4e-7 / 3.4e-7 where the fp32 instruction shows 1.4e-7 / 2.9e-7 / 4.1e-7, and
+// the forward of 8 x 64 x 16 x 56 x 56, K = 128, 2.5e-7 against 3.0e-7.  Over fewer
+// than about six terms the ones left out weigh more than the roundings saved;
+// such layers take the fp32 products.
+//
+// Why.  Dense peaks: fp32 MFMA 157 TFLOP/s, bf16 2.5 PFLOP/s, 419 at six products
+// a term.  Plain loops of the instructions reach 142 and 1.8 PFLOP/s / 6 = 300 (on
+// random values the clock falls to 1.7 GHz), a large library matrix product 153
+// and 1.16 PFLOP/s / 6 = 193.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -262,8 +272,8 @@ struct FuseArgs {
 // without the x and B loads 410, without the pass epilogue 480, without the
 // final stores 475, matrix work and producing alone 260, matrix work alone
 // 180.  The latencies of a step, which all eight waves share through its
-// barrier, not the rate of a unit: vector ALU 47%, addresses 43%, LDS 29%,
-// matrix cores 27% busy.  255 of 256 registers leave no room to load further
+// barrier, not the rate of a unit: vector ALU 47%, addresses 39%, LDS 29%,
+// matrix cores 27% busy.  252 of 256 registers leave no room to load further
 // ahead.  The two-stage form takes 150 us for V and 500 for the product.
 template <int POOL>
 __global__ void __launch_bounds__(512, 2) k_fwd_split(const float* __restrict__ x, const u32x4* __restrict__ P,

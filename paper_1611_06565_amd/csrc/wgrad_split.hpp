@@ -15,8 +15,10 @@
 
 namespace wino {
 
-// Division by a launch constant d >= 1 of values below 2^31: with
-// l = ceil(log2 d) and m = ceil(2^(31 + l) / d), v / d = (v m) >> (31 + l).
+// Division by a launch constant d >= 1 of values below 2^31 by a multiplication
+// (T. Granlund, P. L. Montgomery, "Division by Invariant Integers using
+// Multiplication", PLDI 1994): with l = ceil(log2 d) and m = ceil(2^(31 + l) / d),
+// v / d = (v m) >> (31 + l).
 struct FastDiv {
   uint32_t d, m, s;     // s = l - 1; d = 1: the quotient is v
 };
@@ -65,7 +67,8 @@ struct WgSplitArgs {
 // (8 x 64 x 16 x 56 x 56, K = 128: 567 us with the sum and A'^T, 1069 with V
 // and D in memory): producing and products take turns between the barriers;
 // of the time the vector ALU is busy 47%, addresses 34%, matrix cores 21%, LDS
-// 13%.  Stripped copies: without the loads 415, without the producing 240.
+// 13%.  Stripped copies: without the loads 415, without the producing 240.  256
+// registers, one of them spilled.
 template <int KB>
 __global__ void __launch_bounds__(512, 2) k_wgrad_split(const float* __restrict__ x, const float* __restrict__ dy,
                                                         WgSplitArgs a) {
