@@ -6,14 +6,16 @@ Workload: the F(2^3, 3^3) video layer, batch 8, C = 64 -> K = 128, 16x56x56,
 seed (synthetic stand-ins for C3D activations and weights).
 
 One step is the whole hot path over the batch: kernel transform (a2), input
-transform (a3) and the batched fp32-MFMA GEMM with the fused inverse
-transform (a4 + a5).  Transform synthesis (a1) happens once, at plan time.
+transform (a3) and the batched GEMM with the fused inverse transform (a4 + a5),
+in one kernel or two, on the fp32 matrix cores or with fp32 operands split into
+three bf16 (whatever the plan takes).  Transform synthesis (a1) happens once, at plan time.
 Inputs are resident in HBM before timing starts.  The metric is effective
 TFLOP/s: direct-convolution FLOPs 2*n*K*C*27*prod(Y) per step time.
 
 Prints one JSON line.  Per-stage durations come from HIP events recorded on
 the stream the kernels run on; the roofline object reports the dominant
-kernel against the MI355X fp32 MFMA peak.
+kernel against the MI355X fp32 MFMA peak, a sixth of the bf16 one for the split
+products, or the HBM peak (its field peak_basis).
 """
 import argparse
 import glob
@@ -38,7 +40,7 @@ _COMMON = ["kernels.hpp", "transforms.hpp", "synth.hpp", "layout.hpp", "launch.h
 # the sources that define each kernel family's code (a profile stays valid
 # while they and the plan's launch geometry are unchanged)
 FAMILY_SOURCES = {
-    "m2": _COMMON + ["gemm_acc.hpp", "gemm_split.hpp", "sizes_m2.hip"],
+    "m2": _COMMON + ["gemm_acc.hpp", "gemm_split.hpp", "wgrad_split.hpp", "sizes_m2.hip"],
     "f42": _COMMON + ["gemm_acc.hpp", "gemm_acc4.hpp", "gemm_split.hpp", "gemm_split4.hpp", "sizes_f42.hip"],
     "f43": _COMMON + ["sizes_f43.hip"],
     "f43fused": _COMMON + ["fused43.hpp", "fused_f43.hip"],
@@ -78,7 +80,8 @@ def kernel_hash(desc=None):
             h.update(f.read())
     if desc is not None:
         geo = {k: desc[k] for k in ("T_pad", "C_pad", "K_pad", "block_tiles", "block_kernels", "gemm_parts",
-                                    "gemm_tail_blocks", "fused", "tile")}
+                                    "gemm_tail_blocks", "fused", "tile", "gemm_split", "forward_split",
+                                    "forward_parts")}
         h.update(json.dumps(geo, sort_keys=True).encode())
     return h.hexdigest()[:16]
 
@@ -530,11 +533,9 @@ def main():
     y = plan.new_output()
     torch.cuda.synchronize()
 
-    # F(2^3, 3^3) with whole channel groups and 16-byte rows: the forward forms V
-    # inside the product (wino_forward, include/wino.h)
-    split = (spec.N == 3 and list(d["tile"]) == [2, 2, 2] and spec.r == 3 and not args.no_fuse
-             and plan.C % 16 == 0 and d["X"][2] % 4 == 0 and spec.pad == 1
-             and d["T_pad"] >= (2 if d["T_pad"] >= 512 else 3) * d["K_pad"])
+    # the kernels the plan takes: V formed inside an F(2^3, 3^3) product, and
+    # products on the bf16 matrix cores
+    split = bool(d["forward_split"])
     fused = bool(d["fused"]) or split
 
     # One step: kernel transform, input transform, then the batched GEMM with
@@ -607,7 +608,7 @@ def main():
     if fused:
         # the fused kernel reads x (not V), U, and writes y
         gemm_bytes = 4.0 * (float(np.prod(plan.input_shape)) + nxi * C * K + float(np.prod(plan.output_shape)))
-    peak_mfma = PEAK_SPLIT if split or (spec.N, spec.m, spec.r) == (2, 4, 3) else PEAK_FP32_MFMA
+    peak_mfma = PEAK_SPLIT if split or d["gemm_split"] == 1 else PEAK_FP32_MFMA
     hbm_bound = gemm_flops / gemm_bytes < peak_mfma * 1e12 / (PEAK_HBM * 1e9)
     if hbm_bound:
         achieved = gemm_bytes / (gemm_ms * 1e-3) / 1e9
@@ -691,9 +692,10 @@ def main():
             "tiles": d["T"], "direct_gflop_per_step": flops / 1e9,
         },
         "roofline": {
-            "kernel": ("k_split_u + k_fwd_split + k_part_reduce (input transform in LDS, batched GEMM of fp32 operands "
+            "kernel": ("k_split_u + k_fwd_split%s (input transform in LDS, batched GEMM of fp32 operands "
                        "split into three bf16 on the bf16 matrix cores, fp32 accumulators, fused inverse transform; "
-                       "V never in memory; peak = dense bf16 / 6)" if split else
+                       "V never in memory; peak = dense bf16 / 6)"
+                       % (" + k_part_reduce" if d["forward_parts"] > 1 else "") if split else
                        "k_fused43 (input transform in LDS, batched fp32-MFMA GEMM, fused inverse transform; "
                        "V never in memory)" if fused else
                        "k_gemm_ax (batched fp32-MFMA GEMM, per-axis inverse transform)" if tile else
@@ -705,8 +707,14 @@ def main():
                        if spec.m == 2 and d["gemm_parts"] > 1 else
                        "k_gemm_acc (batched fp32-MFMA GEMM, inverse transform accumulated per pass)"
                        if spec.m == 2 else
-                       "k_gemm_split4 + k_part_reduce (batched GEMM of fp32 operands split into three bf16 on the bf16 "
-                       "matrix cores, fp32 accumulators, fused inverse transform; peak = dense bf16 / 6)"
+                       "k_gemm_split4%s (batched GEMM of fp32 operands split into three bf16 on the bf16 matrix cores, "
+                       "fp32 accumulators, fused inverse transform; %d tail blocks in %d parts each; peak = dense "
+                       "bf16 / 6)" % (" + k_part_reduce" if d["gemm_parts"] > 1 else "", d["gemm_tail_blocks"],
+                                      d["gemm_parts"])
+                       if d["gemm_split"] == 1 else
+                       "k_gemm_split4 (batched fp32-MFMA GEMM, at most four channels, fused inverse transform)"
+                       if d["gemm_split"] == 2 else
+                       "k_gemm_acc4 + k_part_reduce (batched fp32-MFMA GEMM, inverse transform accumulated per pass)"
                        if (spec.N, spec.m, spec.r) == (2, 4, 3) else
                        "k_gemm_inv (batched fp32-MFMA GEMM + fused inverse transform)"),
             "bound": "hbm" if hbm_bound else "mfma",
@@ -718,8 +726,13 @@ def main():
             "algorithmic": ("4*(alpha^N*T*C + alpha^N*C*K + n*K*prod(Y)) = %.4g bytes per launch" % gemm_bytes
                             if hbm_bound else "2*alpha^N*T*C*K = %.4g FLOP per launch" % gemm_flops),
             "gemm_tflops": gemm_flops / (gemm_ms * 1e-3) / 1e12,
-            # MFMA work counted by rocprofv3 (SQ_INSTS_VALU_MFMA_MOPS_F32 x 512)
-            # on these kernel sources, and the MFMA fraction it gives here
+            # what the fraction is of: a sixth of the dense bf16 matrix rate for
+            # the split products (six bf16 products a term), else the fp32 rate
+            "peak_basis": ("HBM" if hbm_bound else
+                           "dense bf16 MFMA / 6" if peak_mfma == PEAK_SPLIT else "dense fp32 MFMA"),
+            # MFMA work counted by rocprofv3 on these kernel sources, in the FLOP
+            # of the terms (SQ_INSTS_VALU_MFMA_MOPS_F32 x 512, or _BF16 x 512 / 6 for
+            # the split products), and the MFMA fraction it gives here
             "mfma_flops_counted": mfma_counted,
             "mfma_frac_counted": (mfma_counted / (gemm_ms * 1e-3) / 1e12 / peak_mfma
                                   if mfma_counted is not None else None),
