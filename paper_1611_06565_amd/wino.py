@@ -149,7 +149,8 @@ class Plan:
     relu=True sets WINO_RELU; leaky=s (a float) sets WINO_LEAKY_RELU with
     slope s (the activation f of eq. 2).  split=False sets WINO_NO_SPLIT: no
     product block is split over several work-groups, whatever the grid size.
-    fuse=False sets WINO_NO_FUSE: an F(4^3) forward stays in two stages.
+    fuse=False sets WINO_NO_FUSE: an F(4^3) or F(2^3) forward stays in two stages.
+    desc holds wino_plan_describe's numbers, the kernels that run among them.
     tile=(m_0, .., m_{N-1}) sets per-axis output tiles (wino_opts.tile)."""
 
     def __init__(self, N, m, r, C, K, dims, pad=0, points=None, relu=False, split=True, leaky=None,
